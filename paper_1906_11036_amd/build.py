@@ -1,7 +1,8 @@
 """Compile libdugks.so for gfx950 with hipcc (in-tree, no JIT cache).
 
-Each source is compiled to its own object in parallel, then the objects are
-linked into one shared library.
+Each source is compiled to its own object in parallel, the two kernel files in
+several parts (the step kernels of one storage or lattice each, PARTS) that are
+joined into one object; the objects are linked into one shared library.
 """
 from __future__ import annotations
 
@@ -17,6 +18,11 @@ OBJ = os.path.join(HERE, "_build")
 SOURCES = [os.path.join(CSRC, "dugks_kernels.hip"), os.path.join(CSRC, "dugks_host.cpp"),
            os.path.join(CSRC, "dugks3d_kernels.hip"), os.path.join(CSRC, "dugks3d_host.cpp"),
            os.path.join(CSRC, "dugks1d.hip")]
+# extra objects of a source: the defines of each part
+PARTS = {"dugks_kernels.hip": [[f"-DDUGKS_PART={st}"] for st in range(4)],
+         "dugks3d_kernels.hip": [[f"-DDUGKS3_Q={q}", f"-DDUGKS3_T={t}"] for q in (19, 15, 7)
+                                 for t in ("double", "float")]}
+LD = os.environ.get("LD", "ld")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # no packed binary32 instructions in device code
@@ -45,27 +51,32 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     headers = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
     headers += [os.path.join(ROOT, "include", f) for f in os.listdir(os.path.join(ROOT, "include"))]
-    jobs = []
+    objs, jobs, joins = [], [], []
     for src in SOURCES:
-        obj = os.path.join(OBJ, os.path.basename(src) + ".o")
+        name = os.path.basename(src)
+        obj = os.path.join(OBJ, name + ".o")
+        objs.append(obj)
         if incremental and not _stale(src, obj, headers):
-            jobs.append((src, obj, None))
             continue
-        jobs.append((src, obj, [HIPCC] + FLAGS + ["-c", src, "-o", obj]))
+        parts = [[]] + PARTS.get(name, [])
+        outs = [obj] if len(parts) == 1 else [os.path.join(OBJ, f"{name}.{k}.o") for k in range(len(parts))]
+        jobs += [(name, [HIPCC] + FLAGS + defs + ["-c", src, "-o", out]) for defs, out in zip(parts, outs)]
+        if len(parts) > 1:
+            joins.append((name, [LD, "-r", "-o", obj] + outs))
     if verbose:
-        for _, _, cmd in jobs:
-            if cmd:
-                print(" ".join(cmd), flush=True)
-    workers = max(1, min(len(jobs), int(os.environ.get("MAX_JOBS", os.cpu_count() or 1))))
-    with ThreadPoolExecutor(max_workers=workers) as ex:
-        results = list(ex.map(lambda j: _run(j[2]) if j[2] else (0, ""), jobs))
-    for (src, _, _), (rc, err) in zip(jobs, results):
-        if rc != 0:
-            raise RuntimeError(f"hipcc failed on {os.path.basename(src)} ({rc}):\n{err}")
-        if verbose and err.strip():
-            print(err)
+        for _, cmd in jobs:
+            print(" ".join(cmd), flush=True)
+    workers = max(1, min(len(jobs) or 1, int(os.environ.get("MAX_JOBS", os.cpu_count() or 1))))
+    for group in (jobs, joins):
+        with ThreadPoolExecutor(max_workers=workers) as ex:
+            results = list(ex.map(lambda j: _run(j[1]), group))
+        for (name, _), (rc, err) in zip(group, results):
+            if rc != 0:
+                raise RuntimeError(f"compiling {name} failed ({rc}):\n{err}")
+            if verbose and err.strip():
+                print(err)
     tmp = LIB + ".tmp"
-    link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + [o for _, o, _ in jobs] + ["-o", tmp]
+    link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", tmp]
     if verbose:
         print(" ".join(link), flush=True)
     rc, err = _run(link)

@@ -1743,6 +1743,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce3(const Inst3* __restrict
   }
 }
 
+#ifndef DUGKS3_Q
 __global__ void k_reduce3_final(const double* __restrict__ partial, int nblocks, double* __restrict__ out) {
   const int v = threadIdx.x;
   if (v >= kRedVals) return;
@@ -1751,18 +1752,30 @@ __global__ void k_reduce3_final(const double* __restrict__ partial, int nblocks,
   out[v] = s;
 }
 
+#endif
 // --------------------------------------------------------------- launch
 static inline hipStream_t S(void* s) { return (hipStream_t)s; }
 
-long long step3_blocks(const Inst3& h, const Launch3& l) {
-  const long long strips = (h.n[0] + kCols - 1) / kCols;
-  const long long tiles = (h.n[1] + l.rows - 1) / l.rows;
-  const long long chunks = (h.n[2] + l.planes - 1) / l.planes;
-  return strips * tiles * chunks;
-}
-
 static size_t step3h_lds_bytes(int q, const Launch3& l) { return (size_t)3 * (l.rows + 2) * q * kLanes * 8; }
 
+// The step kernels are compiled apart from the rest of this file, one object
+// per lattice and storage type (DUGKS3_Q, DUGKS3_T), so that a build runs them
+// in parallel.
+struct Args3;
+template <int Q, typename T>
+int step3_qt(const Args3& a, const Inst3& h, bool walls, long long blocks, const Launch3& l, void* stream);
+
+// The launch arguments of the staged kernel
+struct Args3 {
+  const Inst3* d;
+  int parity;
+  const double* ring;
+  SrcTab ss;
+  int strips, tiles;
+  Batch3 bt;
+};
+
+#ifdef DUGKS3_Q
 template <int Q, int NC, bool WALLS>
 static void step3s_rows(const Inst3* d, int parity, const double* ring, const Launch3& l, int strips, int tiles, dim3 grid,
                         hipStream_t st) {
@@ -1780,11 +1793,11 @@ static void step3h_launch(const Inst3* d, const Inst3& h, int parity, const doub
 }
 // D3Q7, one wave a row: the wall-free instantiation when every axis is
 // periodic and the equilibrium polynomials have at most 4 coefficients
-template <int Q, int NC>
+template <int Q, int NC, typename T>
 static void step3_row_waves(const Inst3* d, const Inst3& h, int parity, const double* ring, const Launch3& l, int strips,
                             int tiles, dim3 grid, hipStream_t st) {
   const bool walls = h.bc[0] != DUGKS_BC_PERIODIC || h.bc[1] != DUGKS_BC_PERIODIC || h.bc[2] != DUGKS_BC_PERIODIC;
-  if (h.storage == DUGKS_F64) {
+  if constexpr (sizeof(T) == 8) {
     if (NC == 8 || walls) step3h_launch<Q, NC, true>(d, h, parity, ring, l, strips, tiles, grid, st);
     else if constexpr (NC != 8) step3h_launch<Q, NC, false>(d, h, parity, ring, l, strips, tiles, grid, st);
   } else {
@@ -1793,15 +1806,6 @@ static void step3_row_waves(const Inst3* d, const Inst3& h, int parity, const do
   }
 }
 
-// The launch arguments of the staged kernel
-struct Args3 {
-  const Inst3* d;
-  int parity;
-  const double* ring;
-  SrcTab ss;
-  int strips, tiles;
-  Batch3 bt;
-};
 template <int Q, int NC, int ROWS, typename T, bool WALLS, bool SRC, bool BATCH>
 static void step3p_go(const Args3& a, const Launch3& l, dim3 grid, hipStream_t st) {
   hipLaunchKernelGGL((k_step3p<Q, NC, ROWS, T, WALLS, SRC, BATCH>), grid, dim3(64 * parts<Q, T, ROWS, WALLS>() * ROWS),
@@ -1831,51 +1835,41 @@ static void step3p_rows(const Args3& a, const Inst3& h, bool walls, const Launch
   else if constexpr (NC != 8) step3p_launch<Q, NC, T, false, false>(a, l, grid, st);
 }
 
-template <int Q>
-static int step3_q(const Args3& a, const Inst3& h, bool walls, long long blocks, const Launch3& l, void* stream) {
-  const int strips = a.strips, tiles = a.tiles;
-  const Inst3* d = a.d;
-  const int parity = a.parity;
-  const double* ring = a.ring;
+template <int Q, int NC, typename T>
+static void step3_nc(const Args3& a, const Inst3& h, bool walls, const Launch3& l, dim3 grid, hipStream_t st) {
+  if constexpr (Q != 7)   // split directions
+    step3p_rows<Q, NC, T>(a, h, walls, l, grid, st);
+  else if (h.src_n > 0)   // D3Q7 with a source: the staged kernel, two parts a row
+    step3p_launch<Q, NC, T, true, true>(a, l, grid, st);
+  else                    // D3Q7: a whole row per wave
+    step3_row_waves<Q, NC, T>(a.d, h, a.parity, a.ring, l, a.strips, a.tiles, grid, st);
+}
+
+template <int Q, typename T>
+int step3_qt(const Args3& a, const Inst3& h, bool walls, long long blocks, const Launch3& l, void* stream) {
   if (blocks <= 0 || blocks > 0x7fffffffLL) return -1;
   const dim3 grid((unsigned)blocks);
-  const int nc = h.ncoef <= 2 ? 2 : (h.ncoef <= 4 ? 4 : 8);
-  if constexpr (Q != 7) {   // split directions
-    if (h.storage == DUGKS_F64) {
-      switch (nc) {
-        case 2: step3p_rows<Q, 2, double>(a, h, walls, l, grid, S(stream)); break;
-        case 4: step3p_rows<Q, 4, double>(a, h, walls, l, grid, S(stream)); break;
-        default: step3p_rows<Q, 8, double>(a, h, walls, l, grid, S(stream)); break;
-      }
-    } else {
-      switch (nc) {
-        case 2: step3p_rows<Q, 2, float>(a, h, walls, l, grid, S(stream)); break;
-        case 4: step3p_rows<Q, 4, float>(a, h, walls, l, grid, S(stream)); break;
-        default: step3p_rows<Q, 8, float>(a, h, walls, l, grid, S(stream)); break;
-      }
-    }
-  } else if (h.src_n > 0) {   // D3Q7 with a source: the staged kernel, two parts a row
-    if (h.storage == DUGKS_F64) {
-      switch (nc) {
-        case 2: step3p_launch<Q, 2, double, true, true>(a, l, grid, S(stream)); break;
-        case 4: step3p_launch<Q, 4, double, true, true>(a, l, grid, S(stream)); break;
-        default: step3p_launch<Q, 8, double, true, true>(a, l, grid, S(stream)); break;
-      }
-    } else {
-      switch (nc) {
-        case 2: step3p_launch<Q, 2, float, true, true>(a, l, grid, S(stream)); break;
-        case 4: step3p_launch<Q, 4, float, true, true>(a, l, grid, S(stream)); break;
-        default: step3p_launch<Q, 8, float, true, true>(a, l, grid, S(stream)); break;
-      }
-    }
-  } else {   // D3Q7: a whole row per wave
-    switch (nc) {
-      case 2: step3_row_waves<Q, 2>(d, h, parity, ring, l, strips, tiles, grid, S(stream)); break;
-      case 4: step3_row_waves<Q, 4>(d, h, parity, ring, l, strips, tiles, grid, S(stream)); break;
-      default: step3_row_waves<Q, 8>(d, h, parity, ring, l, strips, tiles, grid, S(stream)); break;
-    }
+  switch (h.ncoef <= 2 ? 2 : (h.ncoef <= 4 ? 4 : 8)) {
+    case 2: step3_nc<Q, 2, T>(a, h, walls, l, grid, S(stream)); break;
+    case 4: step3_nc<Q, 4, T>(a, h, walls, l, grid, S(stream)); break;
+    default: step3_nc<Q, 8, T>(a, h, walls, l, grid, S(stream)); break;
   }
   return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+template int step3_qt<DUGKS3_Q, DUGKS3_T>(const Args3&, const Inst3&, bool, long long, const Launch3&, void*);
+}  // namespace dugks3
+#else
+long long step3_blocks(const Inst3& h, const Launch3& l) {
+  const long long strips = (h.n[0] + kCols - 1) / kCols;
+  const long long tiles = (h.n[1] + l.rows - 1) / l.rows;
+  const long long chunks = (h.n[2] + l.planes - 1) / l.planes;
+  return strips * tiles * chunks;
+}
+
+template <int Q>
+static int step3_q(const Args3& a, const Inst3& h, bool walls, long long blocks, const Launch3& l, void* stream) {
+  return h.storage == DUGKS_F64 ? step3_qt<Q, double>(a, h, walls, blocks, l, stream)
+                                : step3_qt<Q, float>(a, h, walls, blocks, l, stream);
 }
 
 int launch_step3(const Inst3* d, const Inst3& h, int parity, long long step, const Launch3& l, void* stream) {
@@ -1991,3 +1985,4 @@ int launch_reduce3(const Inst3* d, const Inst3& h, const double* ref, int parity
 }
 
 }  // namespace dugks3
+#endif  // DUGKS3_Q

@@ -1038,6 +1038,7 @@ void k_step(const InstDev* __restrict__ insts,
   }
 }
 
+#ifndef DUGKS_PART
 // Clear slot (step+which)&3 of every instance before a 16-bit step.
 __global__ void k_clear_next_slot(const InstDev* __restrict__ insts, int ninst, long long step,
                                   int which) {
@@ -1045,6 +1046,7 @@ __global__ void k_clear_next_slot(const InstDev* __restrict__ insts, int ninst, 
   if (i < ninst) insts[i].slots[(step + which) & 3] = 0.0f;
 }
 
+#endif
 // ------------------------------------------------------- plain FP64 step
 // One thread per cell; every neighbour value is read from global memory and
 // g of the 3x3 neighbourhood is recomputed per cell.
@@ -1309,6 +1311,7 @@ __global__ void k_get_f(const InstDev* __restrict__ I, double* __restrict__ out,
 }
 
 // ------------------------------------------------------------ reductions
+#ifndef DUGKS_PART
 constexpr int kRedBlocks = 1024;
 constexpr int kRedThreads = 256;
 constexpr int kRedVals = 8;
@@ -1433,13 +1436,17 @@ __global__ void k_fill_u32(unsigned* p, unsigned v, long long n) {
   if (i < n) p[i] = v;
 }
 
+#endif
 // --------------------------------------------------------------- launch
 static inline hipStream_t S(void* s) { return (hipStream_t)s; }
 
 #define DUGKS_CHECK_LAUNCH() return hipGetLastError() == hipSuccess ? 0 : -1
 
+// The step kernels are compiled apart from the rest of this file, one object
+// per storage (DUGKS_PART = the storage), so that a build runs them in parallel.
+#ifdef DUGKS_PART
 template <int Q, int ST>
-static int launch_step_q_st(const StepArgs& a, const Launch& l, void* stream, int measure) {
+int launch_step_q_st(const StepArgs& a, const Launch& l, void* stream, int measure) {
   const int wpb = l.waves_per_block;
   const int blocks_needed = (a.nitems + wpb - 1) / wpb;
   int blocks = blocks_needed;
@@ -1477,6 +1484,12 @@ static int launch_step_q_st(const StepArgs& a, const Launch& l, void* stream, in
 #undef DUGKS_STEP_LAUNCH
   DUGKS_CHECK_LAUNCH();
 }
+template int launch_step_q_st<9, DUGKS_PART>(const StepArgs&, const Launch&, void*, int);
+template int launch_step_q_st<5, DUGKS_PART>(const StepArgs&, const Launch&, void*, int);
+}  // namespace dugks
+#else
+template <int Q, int ST>
+int launch_step_q_st(const StepArgs& a, const Launch& l, void* stream, int measure);
 
 template <int Q>
 static int launch_plain_q(const StepArgs& a, int nx, int ny, void* stream) {
@@ -1641,3 +1654,4 @@ float neq_scale_host(int storage, float m) {
   return storage == DUGKS_BF16NEQ ? neq_scale_for<DUGKS_BF16NEQ>(m) : neq_scale_for<DUGKS_F16NEQ>(m);
 }
 }  // namespace dugks
+#endif  // DUGKS_PART
