@@ -1744,14 +1744,21 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce3(const Inst3* __restrict
 }
 
 #ifndef DUGKS3_Q
-__global__ void k_reduce3_final(const double* __restrict__ partial, int nblocks, double* __restrict__ out) {
-  const int v = threadIdx.x;
-  if (v >= kRedVals) return;
+// One wave a value: its lanes load the kRedBlocks partial sums (all in flight),
+// add their share in block order, then the lanes' tree.  One thread a value
+// walking them took 163 us, this 4 us.
+__global__ __launch_bounds__(64 * 6) void k_reduce3_final(const double* __restrict__ partial,
+                                                          double* __restrict__ out) {
+  const int v = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double t[kRedBlocks / 64];
+#pragma unroll
+  for (int i = 0; i < kRedBlocks / 64; ++i) t[i] = partial[(i * 64 + lane) * kRedVals + v];
   double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += partial[b * kRedVals + v];
-  out[v] = s;
+#pragma unroll
+  for (int i = 0; i < kRedBlocks / 64; ++i) s += t[i];
+  s = wave_sum(s);
+  if (lane == 0) out[v] = s;
 }
-
 #endif
 // --------------------------------------------------------------- launch
 static inline hipStream_t S(void* s) { return (hipStream_t)s; }
@@ -1980,7 +1987,7 @@ int launch_reduce3(const Inst3* d, const Inst3& h, const double* ref, int parity
       break;
   }
   if (hipGetLastError() != hipSuccess) return -1;
-  hipLaunchKernelGGL(k_reduce3_final, dim3(1), dim3(64), 0, S(stream), partial, kRedBlocks, out);
+  hipLaunchKernelGGL(k_reduce3_final, dim3(1), dim3(64 * 6), 0, S(stream), partial, out);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -25,6 +25,8 @@ static constexpr uint32_t kMagicBatch = 0x44554742u;  // "DUGB"
 // multiples of 4, the period of the buffer parity and the 16-bit scale slots.
 static constexpr int kGraphSteps[2] = {32, 4};
 
+static constexpr int kRedOut = 9;   // values of a reduction's result (launch_reduce_widths)
+
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // ------------------------------------------------------------ instance
@@ -330,7 +332,7 @@ struct Engine {
     // room for a work list with the smallest rows-per-wave the tuner may pick
     off += align256(sizeof(WorkItem) * max_items_bound());
     off_partial = off; off += align256(sizeof(double) * 8 * reduce_partials());
-    off_redout = off; off += align256(sizeof(double) * 8);
+    off_redout = off; off += align256(sizeof(double) * kRedOut);
     off_stepbase = off; off += align256(sizeof(long long));
     for (auto& in : inst) {
       in.buf_bytes = in.buffer_bytes(storage);
@@ -760,20 +762,20 @@ struct Engine {
     });
   }
 
-  int reduce(int k, const double* ref, double out[8], unsigned* flags, float slots[4]) {
+  int reduce(int k, const double* ref, double out[6], unsigned* flags, float slots[4]) {
     if (!bound() || !is_ready(k)) return state_error_for(k);
     Instance& in = inst[k];
     int rc = launch_reduce_widths(dev_inst(k), host_table[k], ref, (int)(step & 1), step,
                                   (const double*)(ws + in.off_widths), (double*)(ws + off_partial),
                                   (double*)(ws + off_redout), stream);
     if (rc) return fail(DUGKS_E_HIP, "reduce launch failed");
-    hipError_t e = hipMemcpyAsync(out, ws + off_redout, 8 * sizeof(double), hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess && flags)
-      e = hipMemcpyAsync(flags, ws + in.off_flags, sizeof(unsigned), hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess && slots)
-      e = hipMemcpyAsync(slots, ws + in.off_slots, 4 * sizeof(float), hipMemcpyDeviceToHost, stream);
+    double r[kRedOut];
+    hipError_t e = hipMemcpyAsync(r, ws + off_redout, sizeof(r), hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return hipfail(e, "reduce");
+    memcpy(out, r, 6 * sizeof(double));
+    if (flags) memcpy(flags, r + 6, sizeof(unsigned));
+    if (slots) memcpy(slots, r + 7, 4 * sizeof(float));
     return DUGKS_OK;
   }
 
@@ -1062,7 +1064,7 @@ int dugks_get_f(dugks_ctx* ctx, double* out, int on_device) {
 int dugks_get_diag(dugks_ctx* ctx, dugks_diag* out) {
   GUARD_CTX(ctx);
   if (!out) return ctx->fail(DUGKS_E_ARG, "out is NULL");
-  double r[8];
+  double r[6];
   unsigned flags = 0;
   float slots[4] = {0, 0, 0, 0};
   int rc = ctx->reduce(0, nullptr, r, &flags, slots);
@@ -1087,7 +1089,7 @@ int dugks_get_diag(dugks_ctx* ctx, dugks_diag* out) {
 int dugks_error_norms(dugks_ctx* ctx, const double* ref_dev, double* rel_l2, double* gre) {
   GUARD_CTX(ctx);
   if (!ref_dev || !rel_l2 || !gre) return ctx->fail(DUGKS_E_ARG, "NULL argument");
-  double r[8];
+  double r[6];
   int rc = ctx->reduce(0, ref_dev, r, nullptr, nullptr);
   if (rc) return rc;
   if (r[5] > 0) {   // non-finite cells are left out of the sums: no error to report

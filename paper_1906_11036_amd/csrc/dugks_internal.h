@@ -124,9 +124,11 @@ int launch_get_phi(const InstDev* d, const InstDev& h, double* out, int parity, 
                    void* stream);
 int launch_get_f(const InstDev* d, const InstDev& h, double* out, int parity, long long step,
                  void* stream);
-// Sums over cells into out[0..7] (device): [0] mass, [1] sum|phi-ref|, [2] sum|ref|,
-// [3] sum (phi-ref)^2 |V|, [4] sum ref^2 |V|, [5] non-finite cells.  partial
-// holds reduce_partials() * 8 doubles; widths = dx[0..nx) then dy[0..ny).
+// Sums over cells into out[0..8] (device): [0] mass, [1] sum|phi-ref|, [2] sum|ref|,
+// [3] sum (phi-ref)^2 |V|, [4] sum ref^2 |V|, [5] non-finite cells; then the
+// bytes of the instance's flags (unsigned, at out + 6) and scale slots (4 floats,
+// at out + 7).  partial holds reduce_partials() * 8 doubles; widths = dx[0..nx)
+// then dy[0..ny).
 int launch_reduce_widths(const InstDev* d, const InstDev& h, const double* ref, int parity,
                          long long step, const double* widths, double* partial, double* out,
                          void* stream);
