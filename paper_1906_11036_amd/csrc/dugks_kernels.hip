@@ -981,7 +981,14 @@ __device__ __forceinline__ void step_item(const InstDev* __restrict__ I, const W
   if (__any(bad) && lane == 0) atomicOr(I->flags, (unsigned)DUGKS_FLAG_NONFINITE);
   if (__any(ovf) && lane == 0) atomicOr(I->flags, (unsigned)DUGKS_FLAG_OVERFLOW);
 }
+  // Only updated lanes count: a lane that never enters the branch above may hold
+  // anything in these by now (the compiler moves such a value to and from an
+  // accumulation register under the branch's lane mask, which set the flag at
+  // random in the binary64 step with walls).
+  bad = bad && live;
+  ovf = ovf && live;
 
+    mx = live ? mx : 0.0f;
 // Occupancy target of the step kernel (waves per SIMD): bounds the register
 // allocation so that enough waves stay resident to hide HBM latency.
 #ifndef DUGKS_WAVES_PER_EU_F32
