@@ -974,8 +974,9 @@ __device__ __forceinline__ void step_item(const InstDev* __restrict__ I, const W
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
     if (lane == 0 && mx > 0.0f) {
-      const int slot = measure ? (int)((step + 3) & 3) : (int)(step & 3);
-      atomicMax((unsigned*)(I->slots + slot), __float_as_uint(mx));
+      unsigned* slot = (unsigned*)(I->slots + (measure ? (int)((step + 3) & 3) : (int)(step & 3)));
+      if (__float_as_uint(mx) > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(slot, __float_as_uint(mx));
     }
   }
   if (__any(bad) && lane == 0) atomicOr(I->flags, (unsigned)DUGKS_FLAG_NONFINITE);
