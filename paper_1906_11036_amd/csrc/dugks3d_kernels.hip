@@ -1684,6 +1684,7 @@ __global__ void k_get3(const Inst3* __restrict__ I, double* __restrict__ out, in
   }
 }
 
+#ifndef DUGKS3_Q
 constexpr int kRedBlocks = 1024;
 constexpr int kRedThreads = 256;
 constexpr int kRedVals = 8;
@@ -1743,7 +1744,6 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce3(const Inst3* __restrict
   }
 }
 
-#ifndef DUGKS3_Q
 // One wave a value: its lanes load the kRedBlocks partial sums (all in flight),
 // add their share in block order, then the lanes' tree.  One thread a value
 // walking them took 163 us, this 4 us.

@@ -102,6 +102,9 @@ static void axis_tables(const std::vector<double>& f, int bc, double h, double c
     g[1] = wl / dn;            // normal velocity 0
     g[2] = (wl - h * c) / dn;  // normal velocity +c
   }
+  if (bc == DUGKS_BC_PERIODIC)   // face n is face 0: the same factors to the last bit,
+    for (int m = 0; m < 3; ++m)  // so that either side of the seam computes the same flux
+      geo[(size_t)(n + 1) * kGeo + m] = geo[(size_t)kGeo + m];
   for (int cc = 0; cc < n; ++cc) {
     double* g = &geo[(size_t)(cc + 1) * kGeo];
     g[3] = 0.5 * h * c / (xc[cc + 2] - xc[cc]);
@@ -250,19 +253,22 @@ struct Engine {
   size_t ws_bytes = 0;
   hipStream_t stream = nullptr;
   hipStream_t cap_stream = nullptr;
-  size_t off_table = 0, off_items = 0, off_partial = 0, off_redout = 0, off_stepbase = 0;
+  size_t off_table = 0, off_items = 0, off_items2 = 0, off_partial = 0, off_redout = 0, off_stepbase = 0;
   size_t total_bytes = 0;
   std::vector<InstDev> host_table;
-  std::vector<WorkItem> items;
+  std::vector<WorkItem> items, items2;   // of the one-step and the two-step launches
   Launch launch;
+  bool launch_chosen = false;   // by the caller or the autotuner
   int persistent_blocks = 0;
   // clock: every instance whose ready flag is set holds its state at `step`
   std::vector<char> ready;
   long long step = 0;
+  int cur = 0;   // the buffer that holds the state
   bool need_measure = false;
-  // graphs (kGraphSteps[0] and kGraphSteps[1] steps from a phase-0 step)
-  hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
-  hipGraph_t graph[2] = {nullptr, nullptr};
+  // graphs (kGraphSteps[0] and kGraphSteps[1] steps from a phase-0 step), for
+  // either buffer holding the state
+  hipGraphExec_t graph_exec[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+  hipGraph_t graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
   bool use_graph = true;
   long long graph_steps = 0, eager_steps = 0;   // steps replayed / launched one by one
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -310,8 +316,11 @@ struct Engine {
       in.src_gam[j] = j < n ? gam[j] : 0.0;
     }
     drop_graph();
-    if (launch.waves_per_block > 4 && !wide_blocks_ok()) {   // the source path runs 4-wave blocks
-      const int rc = set_launch(launch.rows_per_wave, 4, launch.schedule, launch.xcd_remap);
+    const Launch before = launch;
+    if (!launch_chosen) default_launch();
+    if (launch.waves_per_block > 4 && !wide_blocks_ok()) launch.waves_per_block = 4;   // the source path runs 4-wave blocks
+    if (launch.rows_per_wave != before.rows_per_wave || launch.waves_per_block != before.waves_per_block) {
+      const int rc = set_launch(launch.rows_per_wave, launch.waves_per_block, launch.schedule, launch.xcd_remap);
       if (rc) return rc;
     }
     return bound() ? upload_tables() : DUGKS_OK;
@@ -331,6 +340,8 @@ struct Engine {
     off_items = off; off += align256(sizeof(WorkItem) * std::max<size_t>(items.size(), 1) * 1);
     // room for a work list with the smallest rows-per-wave the tuner may pick
     off += align256(sizeof(WorkItem) * max_items_bound());
+    off_items2 = off;
+    if (two_storage()) off += align256(sizeof(WorkItem) * max_items_bound(kStripCols2));
     off_partial = off; off += align256(sizeof(double) * 8 * reduce_partials());
     off_redout = off; off += align256(sizeof(double) * kRedOut);
     off_stepbase = off; off += align256(sizeof(long long));
@@ -348,20 +359,80 @@ struct Engine {
     }
     total_bytes = off;
   }
-  size_t max_items_bound() const {
+  size_t max_items_bound(int cols = kStripCols) const {
     size_t n = 0;
-    for (auto& in : inst) n += (size_t)((in.nx + kStripCols - 1) / kStripCols) * (size_t)in.ny;
+    for (auto& in : inst) n += (size_t)((in.nx + cols - 1) / cols) * (size_t)in.ny;
     return n;
   }
-  void build_items() {
-    items.clear();
+  // Storages whose step can run two at a time (a 16-bit step's scale needs the
+  // maximum over the whole grid of the step before).
+  bool two_storage() const { return !plain && !neq(); }
+  // Not where a Dirichlet axis meets a periodic one: a ghost past the periodic
+  // seam has Dirichlet data of its own, which need not be that of the cell it
+  // wraps to, and the two-step launch updates wrapped columns as those cells.
+  bool two_steps_ok() const {
+    for (auto& in : inst)
+      if ((in.bcx == DUGKS_BC_DIRICHLET && in.bcy == DUGKS_BC_PERIODIC) ||
+          (in.bcx == DUGKS_BC_PERIODIC && in.bcy == DUGKS_BC_DIRICHLET))
+        return false;
+    return two_storage() && !any_source();
+  }
+  // Rows a wave marches when the caller has not chosen: a SIMD runs k = waves /
+  // 1024 of them, each H rows and a prologue worth c rows, and more than one at
+  // a time only fills the gaps of a row's latency: cost max(1, v k) (H + c).
+  // Binary32 and the 16-bit formats reach v = 0.75 with two or more waves a
+  // SIMD, binary64 and the sources hold one (v = 1).  Measured, two steps a
+  // launch, us a step over H: 512^2 binary32 8.6 (1), 6.1 (3), 6.2 (6), 11.0
+  // (16); 1024^2 15.2 (4), 14.3 (12), 16.3 (24), 36.6 (64); 4096^2 174 (8), 151
+  // (48), 165 (64); binary64 512^2 12.8 (2), 9.1 (6), 13.6 (12); 128^2 3.7 (1),
+  // 27.3 (32).
+  int default_rows() const {
+    const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48};
+    const bool two = two_steps_ok();
+    const double v = (storage == DUGKS_F64 || any_source()) ? 1.0 : 0.75, c = two ? 3.5 : (neq() ? 1.5 : 2.5);
+    const int cols = two ? kStripCols2 : kStripCols;
+    double best_cost = 0;
+    int best = 0;
+    for (int H : cand) {
+      double waves = 0;
+      for (auto& in : inst) waves += (double)((in.nx + cols - 1) / cols) * ((in.ny + H - 1) / H);
+      const double k = waves / 1024.0;
+      const double cost = std::max(1.0, v * (k < 8 ? std::ceil(k) : k)) * (H + c);
+      if (best == 0 || cost <= best_cost) { best_cost = cost; best = H; }
+    }
+    return best;
+  }
+  // The default launch: blocks of 4 waves (binary64: 2) once they fill the chip
+  // several times over, single waves before (they spread over more CUs).
+  void default_launch() {
+    launch = Launch{};
+    launch.rows_per_wave = default_rows();
+    double waves = 0;
+    for (auto& in : inst)
+      waves += (double)((in.nx + kStripCols - 1) / kStripCols) * ((in.ny + launch.rows_per_wave - 1) / launch.rows_per_wave);
+    launch.waves_per_block = waves < 4096 ? 1 : (storage == DUGKS_F64 ? 2 : 4);
+  }
+  void build_items_of(std::vector<WorkItem>& out, int cols) const {
+    out.clear();
     const int H = launch.rows_per_wave;
     for (int k = 0; k < (int)inst.size(); ++k) {
       const Instance& in = inst[k];
       for (int y0 = 0; y0 < in.ny; y0 += H)
-        for (int x0 = 0; x0 < in.nx; x0 += kStripCols)
-          items.push_back(WorkItem{k, x0, y0, std::min(y0 + H, in.ny)});
+        for (int x0 = 0; x0 < in.nx; x0 += cols)
+          out.push_back(WorkItem{k, x0, y0, std::min(y0 + H, in.ny)});
     }
+  }
+  void build_items() {
+    build_items_of(items, kStripCols);
+    if (two_storage()) build_items_of(items2, kStripCols2);
+  }
+  hipError_t upload_items() {
+    hipError_t e = hipMemcpyAsync(ws + off_items, items.data(), sizeof(WorkItem) * items.size(),
+                                  hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess && !items2.empty())
+      e = hipMemcpyAsync(ws + off_items2, items2.data(), sizeof(WorkItem) * items2.size(), hipMemcpyHostToDevice,
+                         stream);
+    return e;
   }
 
   void fill_table() {
@@ -430,8 +501,7 @@ struct Engine {
     hipError_t e = hipMemcpyAsync(ws + off_table, host_table.data(), sizeof(InstDev) * inst.size(),
                                   hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return hipfail(e, "upload instance table");
-    e = hipMemcpyAsync(ws + off_items, items.data(), sizeof(WorkItem) * items.size(),
-                       hipMemcpyHostToDevice, stream);
+    e = upload_items();
     if (e != hipSuccess) return hipfail(e, "upload work list");
     for (auto& in : inst) {
       struct { size_t off; const void* src; size_t n; } cp[] = {
@@ -476,6 +546,7 @@ struct Engine {
       persistent_blocks = 256 * 4;
     ready.assign(inst.size(), 0);
     step = 0;
+    cur = 0;
     int rc = upload_tables();
     if (rc) return rc;
     for (auto& in : inst) {
@@ -496,12 +567,13 @@ struct Engine {
   const InstDev* dev_table() const { return (const InstDev*)(ws + off_table); }
   const InstDev* dev_inst(int k) const { return dev_table() + k; }
 
-  StepArgs step_args(long long n) const {
+  // step n with the state in buffer `buf`
+  StepArgs step_args(long long n, int buf) const {
     StepArgs a{};
     a.insts = dev_table();
     a.items = (const WorkItem*)(ws + off_items);
     a.nitems = (int)items.size();
-    a.parity = (int)(n & 1);
+    a.parity = buf;
     a.step = n;
     a.q = inst[0].q;
     a.storage = storage;
@@ -540,6 +612,7 @@ struct Engine {
   void restart_clock_for(int k) {
     if (step != 0 || ready.size() != inst.size()) ready.assign(inst.size(), 0);
     step = 0;
+    cur = 0;   // initialisations write buffer 0
     ready[k] = 1;
   }
   // Dirichlet data covers steps [step, step + n)
@@ -551,14 +624,19 @@ struct Engine {
     return true;
   }
 
-  // Enqueue one step with input index n on stream s (captured: index n after
-  // the base written before each replay).
-  int enqueue_step(long long n, hipStream_t s, bool measure, bool captured = false) {
-    StepArgs a = step_args(n);
+  // Enqueue step n (count == 2: steps n and n + 1 in one launch) on stream s,
+  // from buffer buf into the other (captured: index n after the base written
+  // before each replay).
+  int enqueue_step(long long n, int buf, int count, hipStream_t s, bool measure, bool captured = false) {
+    StepArgs a = step_args(n, buf);
     if (captured) a.step_base = (const long long*)(ws + off_stepbase);
     int rc;
     if (plain) {
       rc = launch_step_plain(a, inst[0].nx, inst[0].ny, s);
+    } else if (count == 2) {
+      a.items = (const WorkItem*)(ws + off_items2);
+      a.nitems = (int)items2.size();
+      rc = launch_step2(a, launch, s);
     } else {
       if (neq()) {
         rc = launch_clear_slot(dev_table(), (int)inst.size(), n, measure ? 3 : 0, s);
@@ -571,25 +649,30 @@ struct Engine {
   }
 
   void drop_graph() {
-    for (int w = 0; w < 2; ++w) {
-      if (graph_exec[w]) { (void)hipGraphExecDestroy(graph_exec[w]); graph_exec[w] = nullptr; }
-      if (graph[w]) { (void)hipGraphDestroy(graph[w]); graph[w] = nullptr; }
-    }
+    for (int w = 0; w < 2; ++w)
+      for (int b = 0; b < 2; ++b) {
+        if (graph_exec[w][b]) { (void)hipGraphExecDestroy(graph_exec[w][b]); graph_exec[w][b] = nullptr; }
+        if (graph[w][b]) { (void)hipGraphDestroy(graph[w][b]); graph[w][b] = nullptr; }
+      }
   }
 
-  // Capture kGraphSteps[w] steps starting at step index 0; replayed at any step
-  // divisible by 4 (same buffer parity and 16-bit slot phase).
-  int build_graph(int w) {
+  // Capture kGraphSteps[w] steps starting at step index 0 from buffer b;
+  // replayed at any step divisible by 4 (same 16-bit slot phase).  The number of
+  // launches is even, so the state is in buffer b again after a replay.
+  int build_graph(int w, int b) {
     hipError_t e = hipStreamBeginCapture(cap_stream, hipStreamCaptureModeRelaxed);
     if (e != hipSuccess) return hipfail(e, "begin capture");
     int rc = DUGKS_OK;
-    for (int k = 0; k < kGraphSteps[w] && rc == DUGKS_OK; ++k) rc = enqueue_step(k, cap_stream, false, true);
+    const int count = two_steps_ok() ? 2 : 1;
+    int buf = b;
+    for (int k = 0; k < kGraphSteps[w] && rc == DUGKS_OK; k += count, buf ^= 1)
+      rc = enqueue_step(k, buf, count, cap_stream, false, true);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(cap_stream, &g);
     if (rc) { if (g) (void)hipGraphDestroy(g); return rc; }
     if (e != hipSuccess) return hipfail(e, "end capture");
-    graph[w] = g;
-    e = hipGraphInstantiate(&graph_exec[w], graph[w], nullptr, nullptr, 0);
+    graph[w][b] = g;
+    e = hipGraphInstantiate(&graph_exec[w][b], graph[w][b], nullptr, nullptr, 0);
     if (e != hipSuccess) { drop_graph(); return hipfail(e, "instantiate graph"); }
     return DUGKS_OK;
   }
@@ -605,29 +688,32 @@ struct Engine {
     const bool graphable = use_graph && !plain;
     while (remaining > 0) {
       if (need_measure) {
-        int rc = enqueue_step(step, stream, true);
+        int rc = enqueue_step(step, cur, 1, stream, true);
         if (rc) return rc;
         need_measure = false;
       }
       const int w = remaining >= kGraphSteps[0] ? 0 : 1;
       if (graphable && remaining >= kGraphSteps[1] && (step & 3) == 0) {
-        if (!graph_exec[w]) {
-          int rc = build_graph(w);
+        if (!graph_exec[w][cur]) {
+          int rc = build_graph(w, cur);
           if (rc) return rc;
         }
         if (launch_set_i64((long long*)(ws + off_stepbase), step, stream))
           return fail(DUGKS_E_HIP, "step base launch failed");
-        hipError_t e = hipGraphLaunch(graph_exec[w], stream);
+        hipError_t e = hipGraphLaunch(graph_exec[w][cur], stream);
         if (e != hipSuccess) return hipfail(e, "graph launch");
         step += kGraphSteps[w];
         remaining -= kGraphSteps[w];
         graph_steps += kGraphSteps[w];
       } else {
-        int rc = enqueue_step(step, stream, false);
+        // pairs start at even steps, so that a run reaches the graphs' phase
+        const int count = remaining >= 2 && (step & 1) == 0 && two_steps_ok() ? 2 : 1;
+        int rc = enqueue_step(step, cur, count, stream, false);
         if (rc) return rc;
-        step += 1;
-        remaining -= 1;
-        eager_steps += 1;
+        cur ^= 1;
+        step += count;
+        remaining -= count;
+        eager_steps += count;
       }
     }
     return DUGKS_OK;
@@ -649,14 +735,19 @@ struct Engine {
       persistent_blocks = cus * (16 / wpb);
       build_items();
       if (items.size() > max_items_bound() + 1) return fail(DUGKS_E_ARG, "work list too long");
-      hipError_t e = hipMemcpyAsync(ws + off_items, items.data(), sizeof(WorkItem) * items.size(),
-                                    hipMemcpyHostToDevice, stream);
+      hipError_t e = upload_items();
       if (e != hipSuccess) return hipfail(e, "upload work list");
       e = hipStreamSynchronize(stream);
       if (e != hipSuccess) return hipfail(e, "synchronise");
     }
     drop_graph();
     return DUGKS_OK;
+  }
+
+  int choose_launch(int rows, int wpb, int sched, int xcd) {
+    const int rc = set_launch(rows, wpb, sched, xcd);
+    if (rc == DUGKS_OK) launch_chosen = true;
+    return rc;
   }
 
   int set_phi(int k, const double* phi, int on_device) {
@@ -749,7 +840,7 @@ struct Engine {
     if (!out) return fail(DUGKS_E_ARG, "out is NULL");
     const Instance& in = inst[k];
     return read_out((size_t)in.cells() * sizeof(double), out, on_device, [&](double* dst) {
-      return launch_get_phi(dev_inst(k), host_table[k], dst, (int)(step & 1), step, stream);
+      return launch_get_phi(dev_inst(k), host_table[k], dst, cur, step, stream);
     });
   }
 
@@ -758,14 +849,14 @@ struct Engine {
     if (!out) return fail(DUGKS_E_ARG, "out is NULL");
     const Instance& in = inst[k];
     return read_out((size_t)in.cells() * in.q * sizeof(double), out, on_device, [&](double* dst) {
-      return launch_get_f(dev_inst(k), host_table[k], dst, (int)(step & 1), step, stream);
+      return launch_get_f(dev_inst(k), host_table[k], dst, cur, step, stream);
     });
   }
 
   int reduce(int k, const double* ref, double out[6], unsigned* flags, float slots[4]) {
     if (!bound() || !is_ready(k)) return state_error_for(k);
     Instance& in = inst[k];
-    int rc = launch_reduce_widths(dev_inst(k), host_table[k], ref, (int)(step & 1), step,
+    int rc = launch_reduce_widths(dev_inst(k), host_table[k], ref, cur, step,
                                   (const double*)(ws + in.off_widths), (double*)(ws + off_partial),
                                   (double*)(ws + off_redout), stream);
     if (rc) return fail(DUGKS_E_HIP, "reduce launch failed");
@@ -792,8 +883,9 @@ struct Engine {
     return DUGKS_OK;
   }
 
-  // Time candidate launch configurations on the inactive buffer only: the
-  // step writes buffer (step+1)&1 and never swaps, so the state is kept.
+  // Time candidate launch configurations on the inactive buffer only (the
+  // buffers are not swapped, so the state is kept), two steps a launch where
+  // runs of steps take them so.
   int autotune(int trials) {
     if (!bound()) return fail(DUGKS_E_STATE, "not bound");
     if (!all_ready()) return state_error();
@@ -801,6 +893,7 @@ struct Engine {
     if (plain) return DUGKS_OK;
     // every trial step reads the Dirichlet data of the current step
     if (!rings_cover(1)) return fail(DUGKS_E_STATE, "Dirichlet data does not cover the current step");
+    const int count = two_steps_ok() && rings_cover(2) ? 2 : 1;
     // keep the 16-bit slots: the trial steps accumulate into them
     std::vector<std::vector<float>> saved(inst.size(), std::vector<float>(4));
     for (size_t k = 0; k < inst.size(); ++k) {
@@ -813,7 +906,7 @@ struct Engine {
     const Launch keep = launch;
     Launch best = keep;
     float best_ms = 1e30f;
-    const int rows_c[] = {2, 4, 8, 16, 32, 64, 128};   // short items: more waves on small grids
+    const int rows_c[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 128};   // short items: more waves on small grids
     const int wpb_c[] = {1, 2, 4, 8};
     for (int sched = 0; sched < 2; ++sched)
       for (int rows : rows_c)
@@ -822,10 +915,10 @@ struct Engine {
           if (set_launch(rows, wpb, sched, 1)) return DUGKS_E_ARG;
           // warm-up
           for (int t = 0; t < 2; ++t)
-            if (enqueue_step(step, stream, false)) return DUGKS_E_HIP;
+            if (enqueue_step(step, cur, count, stream, false)) return DUGKS_E_HIP;
           e = hipEventRecord(ev0, stream);
           for (int t = 0; t < trials && e == hipSuccess; ++t)
-            if (enqueue_step(step, stream, false)) return DUGKS_E_HIP;
+            if (enqueue_step(step, cur, count, stream, false)) return DUGKS_E_HIP;
           if (e == hipSuccess) e = hipEventRecord(ev1, stream);
           if (e == hipSuccess) e = hipEventSynchronize(ev1);
           float ms = 0;
@@ -833,7 +926,7 @@ struct Engine {
           if (e != hipSuccess) return hipfail(e, "autotune timing");
           if (ms < best_ms) { best_ms = ms; best = launch; }
         }
-    int rc = set_launch(best.rows_per_wave, best.waves_per_block, best.schedule, best.xcd_remap);
+    int rc = choose_launch(best.rows_per_wave, best.waves_per_block, best.schedule, best.xcd_remap);
     if (rc) return rc;
     for (size_t k = 0; k < inst.size(); ++k) {
       e = hipMemcpyAsync(ws + inst[k].off_slots, saved[k].data(), 4 * sizeof(float),
@@ -862,7 +955,7 @@ struct Engine {
     o->state_bytes = in.buffer_bytes(storage);
     o->graph_steps = graph_steps;
     o->eager_steps = eager_steps;
-    o->xy_symmetric = step_args(0).sym;
+    o->xy_symmetric = step_args(0, 0).sym;
   }
 
   ~Engine() {
@@ -980,7 +1073,7 @@ int dugks_create(dugks_ctx** out, int nx, int ny, const double* xf, const double
   dugks::equilibrium_polys(c->inst[0]);
   c->storage = p->storage;
   c->plain = p->kernel == DUGKS_KERNEL_PLAIN;
-  if (c->storage == DUGKS_F64) { c->launch.rows_per_wave = 32; c->launch.waves_per_block = 1; }
+  c->default_launch();
   *out = c;
   return DUGKS_OK;
 }
@@ -1107,7 +1200,7 @@ int dugks_error_norms_noalloc(dugks_ctx* ctx, const double* ref_dev, double* out
   if (!ctx->bound() || !ctx->all_ready()) return ctx->fail(DUGKS_E_STATE, "no state");
   const dugks::Instance& in = ctx->inst[0];
   const int rc = dugks::launch_norms_noalloc(ctx->dev_inst(0), ctx->host_table[0], ref_dev,
-                                             (int)(ctx->step & 1), ctx->step,
+                                             ctx->cur, ctx->step,
                                              (const double*)(ctx->ws + in.off_widths), out_dev,
                                              ctx->stream);
   if (rc == -2) return ctx->fail(DUGKS_E_HIP, "hipGetSymbolAddress of the reduction scratch failed");
@@ -1136,7 +1229,7 @@ int dugks_checkpoint(dugks_ctx* ctx, void* host_buf, size_t* len) {
   hd.params_hash = dugks::params_hash(in, ctx->storage);
   hd.payload_bytes = payload;
   char* dst = (char*)host_buf + sizeof(hd);
-  hipError_t e = hipMemcpyAsync(dst, ctx->ws + in.off_buf[ctx->step & 1], payload,
+  hipError_t e = hipMemcpyAsync(dst, ctx->ws + in.off_buf[ctx->cur], payload,
                                 hipMemcpyDeviceToHost, ctx->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(hd.slots, ctx->ws + in.off_slots, sizeof(hd.slots), hipMemcpyDeviceToHost, ctx->stream);
@@ -1168,7 +1261,7 @@ int dugks_restore(dugks_ctx* ctx, const void* host_buf, size_t len) {
   const char* src = (const char*)host_buf + sizeof(hd);
   if (dugks::fnv1a(src, payload) != hd.payload_checksum) return ctx->fail(DUGKS_E_FORMAT, "checksum mismatch");
   if (hd.step < 0) return ctx->fail(DUGKS_E_FORMAT, "negative step");
-  hipError_t e = hipMemcpyAsync(ctx->ws + in.off_buf[hd.step & 1], src, payload, hipMemcpyHostToDevice,
+  hipError_t e = hipMemcpyAsync(ctx->ws + in.off_buf[0], src, payload, hipMemcpyHostToDevice,
                                 ctx->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(ctx->ws + in.off_slots, hd.slots, sizeof(hd.slots), hipMemcpyHostToDevice, ctx->stream);
@@ -1178,6 +1271,7 @@ int dugks_restore(dugks_ctx* ctx, const void* host_buf, size_t len) {
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) return ctx->hipfail(e, "restore copy");
   ctx->step = hd.step;
+  ctx->cur = 0;
   ctx->ready.assign(1, 1);
   ctx->need_measure = false;
   return DUGKS_OK;
@@ -1185,7 +1279,7 @@ int dugks_restore(dugks_ctx* ctx, const void* host_buf, size_t len) {
 
 int dugks_set_launch(dugks_ctx* ctx, int rows, int wpb, int sched, int xcd) {
   GUARD_CTX(ctx);
-  return ctx->set_launch(rows, wpb, sched, xcd);
+  return ctx->choose_launch(rows, wpb, sched, xcd);
 }
 
 int dugks_autotune(dugks_ctx* ctx, int trial_steps) {
@@ -1216,7 +1310,6 @@ int dugks_batch_create(dugks_batch** out, int n, const dugks_instance_desc* d, i
   if (n < 1 || !d) return b->fail(DUGKS_E_ARG, "empty batch");
   if (storage < DUGKS_F64 || storage > DUGKS_BF16NEQ) return b->fail(DUGKS_E_UNSUPPORTED, "unknown storage");
   b->storage = storage;
-  if (storage == DUGKS_F64) { b->launch.rows_per_wave = 32; b->launch.waves_per_block = 1; }
   b->inst.resize(n);
   for (int k = 0; k < n; ++k) {
     dugks_params p = d[k].p;
@@ -1231,6 +1324,7 @@ int dugks_batch_create(dugks_batch** out, int n, const dugks_instance_desc* d, i
     if (rc == 0) rc = dugks::set_D_impl(b->inst[k], d[k].d_deg, d[k].dxx, d[k].dxy, d[k].dyy, b->err);
     if (rc) { b->err = "instance " + std::to_string(k) + ": " + b->err; return rc; }
   }
+  b->default_launch();
   return DUGKS_OK;
 }
 
@@ -1276,7 +1370,7 @@ int dugks_batch_autotune(dugks_batch* b, int trial_steps) {
 
 int dugks_batch_set_launch(dugks_batch* b, int rows, int wpb, int sched, int xcd) {
   GUARD_BATCH(b);
-  return b->set_launch(rows, wpb, sched, xcd);
+  return b->choose_launch(rows, wpb, sched, xcd);
 }
 
 int dugks_batch_step(dugks_batch* b, int nsteps) {

@@ -6,7 +6,8 @@
 //   DUGKS_F32   : P = q planes of float
 //   16-bit neq  : plane 0 = phi (float, 4-byte elements), planes 1..q-1 = g_i
 //                 (2-byte elements, g_0 = -sum g_i is not stored)
-// Two buffers per instance (ping-pong): step n reads buffer n%2, writes the other.
+// Two buffers per instance (ping-pong): a launch, which takes one or two steps,
+// reads the buffer that holds the state and writes the other.
 #pragma once
 
 #include <stdint.h>
@@ -19,6 +20,7 @@ constexpr int kMaxQ = 9;
 constexpr int kMaxCoef = 8;     // E_i(phi) has degree <= 7 (C has degree 2*4-1)
 constexpr int kStripLanes = 64; // one wave covers 64 columns ...
 constexpr int kStripCols = 62;  // ... of which 62 are updated; lanes 0 and 63 are halo
+constexpr int kStripCols2 = 60; // columns updated by a wave that takes two steps (two halo lanes each side)
 constexpr int kGeo = 5;
 constexpr int kRhoCoef = 4;     // B'(phi) has degree <= 3
 constexpr int kMaxSrcTerms = DUGKS_MAX_SRC_TERMS;
@@ -112,6 +114,10 @@ struct StepArgs {
 };
 
 int launch_step_fused(const StepArgs& a, const Launch& l, void* stream, int measure);
+// steps a.step and a.step + 1 in one launch over a work list of kStripCols2-column
+// strips (binary32 / binary64 storage, no source); the state after the second
+// goes to buffer parity ^ 1
+int launch_step2(const StepArgs& a, const Launch& l, void* stream);
 int launch_step_plain(const StepArgs& a, int nx, int ny, void* stream);
 // zero slots[(step + which) & 3] of every instance
 int launch_clear_slot(const InstDev* insts, int ninst, long long step, int which, void* stream);

@@ -552,6 +552,18 @@ __device__ __forceinline__ int src_index(int i, int n, int bc) {
   return i < 0 ? 0 : n - 1;
 }
 
+// The same for up to two cells past either end (wrapped as often as that takes
+// on a mesh of one cell), in arithmetic only: the index is often wave-uniform,
+// and as branches it split the row loops into small blocks.
+__device__ __forceinline__ int src_index2(int i, int n, int bc) {
+  int w = i + (n & (i >> 31));
+  w += n & (w >> 31);
+  w -= n & ~((w - n) >> 31);
+  w -= n & ~((w - n) >> 31);
+  const int k = min(max(i, 0), n - 1);
+  return bc == DUGKS_BC_PERIODIC ? w : k;
+}
+
 // Pairwise sum of N values.
 template <int N, typename T> __device__ __forceinline__ T tree_sum(const T* v) {
   if constexpr (N == 1) return v[0];
@@ -969,10 +981,20 @@ __device__ __forceinline__ void step_item(const InstDev* __restrict__ I, const W
   }
   if (j < y1) body(j, S0{});
   if (j + 1 < y1) body(j + 1, S1{});
+  // Only updated lanes count: a lane that never enters the branch above may hold
+  // anything in these by now (the compiler moves such a value to and from an
+  // accumulation register under the branch's lane mask, which set the flag at
+  // random in the binary64 step with walls).
+  bad = bad && live;
+  ovf = ovf && live;
   if constexpr (Stor<ST>::neq) {
+    mx = live ? mx : 0.0f;
     // wave maximum of |f~_i - E_i| (i >= 1) over updated cells -> the instance's slot
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    // Every wave of the instance aims at one address: a wave whose maximum does
+    // not exceed what it reads there leaves the atomic out (the value only
+    // grows, so a stale read costs an atomic and no more).
     if (lane == 0 && mx > 0.0f) {
       unsigned* slot = (unsigned*)(I->slots + (measure ? (int)((step + 3) & 3) : (int)(step & 3)));
       if (__float_as_uint(mx) > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
@@ -982,14 +1004,7 @@ __device__ __forceinline__ void step_item(const InstDev* __restrict__ I, const W
   if (__any(bad) && lane == 0) atomicOr(I->flags, (unsigned)DUGKS_FLAG_NONFINITE);
   if (__any(ovf) && lane == 0) atomicOr(I->flags, (unsigned)DUGKS_FLAG_OVERFLOW);
 }
-  // Only updated lanes count: a lane that never enters the branch above may hold
-  // anything in these by now (the compiler moves such a value to and from an
-  // accumulation register under the branch's lane mask, which set the flag at
-  // random in the binary64 step with walls).
-  bad = bad && live;
-  ovf = ovf && live;
 
-    mx = live ? mx : 0.0f;
 // Occupancy target of the step kernel (waves per SIMD): bounds the register
 // allocation so that enough waves stay resident to hide HBM latency.
 #ifndef DUGKS_WAVES_PER_EU_F32
@@ -1042,6 +1057,237 @@ void k_step(const InstDev* __restrict__ insts,
       step_item<Q, ST, NC, true, NF, SYM>(I, it, parity, step, lane, measure != 0);
     else
       step_item<Q, ST, NC, false, NF, SYM>(I, it, parity, step, lane, measure != 0);
+    if (!persistent) break;
+  }
+}
+
+// ----------------------------------------------------- two steps in one pass
+// One wave takes a work item through two steps without the state between them
+// touching memory: the rows stream through two windows in registers, the first
+// made from the loaded f~, the second from the first step's result of the same
+// row.  Each step eats one column at either end of the wave and one row at
+// either end of the chunk, so lanes 2..61 are updated (60 columns) and a chunk
+// of H rows reads H + 4 and runs the first step on H + 2.  What is computed for
+// a cell, and its order, is that of step_item: the results are the same bits.
+// Without a source, binary32 and binary64 storage (the 16-bit formats' scale of
+// a step needs the maximum over the whole grid of the step before).
+template <int Q, int ST, int NC, bool GH, bool SYM = false>
+__device__ __forceinline__ void step2_item(const InstDev* __restrict__ I, const WorkItem it, int parity,
+                                           long long step, int lane) {
+  using T = typename Stor<ST>::T;
+  using C = Coef<T>;
+  static_assert(!Stor<ST>::neq, "binary32 / binary64 storage");
+  Eq<T, Q, NC, SYM> eq;
+  eq.load(I);
+  const int nx = I->nx, ny = I->ny, pitch = I->pitch, bcx = I->bcx, bcy = I->bcy;
+  const unsigned plane = (unsigned)I->plane;
+  const __amdgpu_buffer_rsrc_t Rin = rsrc(I->buf[parity], I->buf_bytes);
+  const __amdgpu_buffer_rsrc_t Rout = rsrc(I->buf[parity ^ 1], I->buf_bytes);
+  const bool per_x = bcx == DUGKS_BC_PERIODIC, per_y = bcy == DUGKS_BC_PERIODIC;
+
+  const int c = it.x0 - 2 + lane;
+  // lanes past nx + 1 are not needed: they repeat column nx + 1
+  const int cc = c < nx + 1 ? c : nx + 1;
+  const int sc_col = src_index2(cc, nx, bcx);
+  const bool wall_x = (c < 0 || c >= nx) && !per_x;
+  const bool live = lane >= 2 && lane <= kStripCols2 + 1 && c < nx;
+
+  // West face: the table's face c where it has one, a wrapped column's otherwise;
+  // tangential and update factors of the (wrapped) column.
+  const T* cf = C::col(I) + (long long)((cc >= 0 && cc <= nx ? cc : sc_col) + 1) * kGeo;
+  const T* cg = C::col(I) + (long long)(sc_col + 1) * kGeo;
+  const T cam = cf[0], ca0 = cf[1], cap = cf[2], ctau = cg[3], ck = cg[4];
+  const CPtr<T> rg = as_constant(C::row(I));
+  auto row_face = [&](int r) -> CPtr<T> {   // the face below row r
+    const int f = src_index2(r, ny, bcy);
+    return rg + (long long)((r == ny ? r : f) + 1) * kGeo;
+  };
+  auto row_cell = [&](int r) -> CPtr<T> { return rg + (long long)(src_index2(r, ny, bcy) + 1) * kGeo; };
+  const double* ring[2] = {nullptr, nullptr};
+  if (GH && I->ring != nullptr) {
+    ring[0] = I->ring + step * I->ring_len;
+    ring[1] = ring[0] + I->ring_len;
+  }
+  auto row_idx = [&](int r) -> unsigned { return (unsigned)(src_index2(r, ny, bcy) * pitch + sc_col); };
+
+  const int y0 = it.y0, y1 = it.y1;
+  // Per step s and row slot (row - y0 + 1) % 3, as in step_item
+  T G[2][3][Q], LS[2][3][Q], FT[2][3][Q], SX[2][3][Q], FY[2][3][Q];
+  Raw<Q, ST> RW[3], M;   // rows of f~ loaded; the first step's result of one row
+
+  auto make_row = [&](auto st, const Raw<Q, ST>& raw, int r, T* g, T* ftp, bool want_ftp) {
+    constexpr int s = decltype(st)::value;
+    T phi_a;
+    cell_g<Q, ST, NC, 0>(I, eq, raw, Scales{1.0f, 1.0f}, g, ftp, want_ftp, phi_a);
+    if constexpr (GH) {
+      const bool wall_y = (r < 0 || r >= ny) && !per_y;
+      if (wall_x || wall_y) {
+        double pg = 0.0;
+        if (ring[s] != nullptr) pg = ring[s][ring_index(nx, ny, c < -1 ? -1 : (c > nx ? nx : c), r)];
+        ghost_g<Q, ST, NC>(I, eq, g, phi_a, wall_x, wall_y, pg);
+      }
+    }
+  };
+  // the second step's raw values: the first step's result, a wall lane taking
+  // the column next to the wall (whose distribution a ghost copies)
+  auto second_raw = [&](const T* o) {
+#pragma unroll
+    for (int k = 0; k < Q; ++k) M.v[k] = o[k];
+    if constexpr (GH) {
+      if (!per_x) {
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+          const T e = shl1(o[k]), w = shr1(o[k]);
+          M.v[k] = c < 0 ? e : (c >= nx ? w : o[k]);
+        }
+      }
+    }
+  };
+  auto slopes = [&](auto st, int slot) {   // west values and x-slope numerators of the row in a slot
+    constexpr int s = decltype(st)::value;
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+      LS[s][slot][k] = shr1(G[s][slot][k]);
+      if (lat_cx(k) != 0) SX[s][slot][k] = shl1(G[s][slot][k]) - LS[s][slot][k];
+    }
+  };
+  auto y_face = [&](auto st, int lo, int hi, int r) {   // face below row r, between the rows in lo and hi
+    constexpr int s = decltype(st)::value;
+    const CPtr<T> g = row_face(r);
+    T ts[Q];
+#pragma unroll
+    for (int k = 0; k < Q; ++k)
+      if (lat_cx(k) != 0) ts[k] = SX[s][lo][k] + SX[s][hi][k];
+    face<Q, NC, 1, T, 0>(eq, G[s][lo], G[s][hi], ts, g[0], g[1], g[2], ctau, FY[s][lo]);
+  };
+  // the rest of row j of step s: rows j - 1, j, j + 1 in slots sm, s0, sp
+  auto finish_row = [&](auto st, int sm, int s0, int sp, int j, T* o) {
+    constexpr int s = decltype(st)::value;
+    slopes(st, sp);
+    y_face(st, s0, sp, j + 1);
+    const CPtr<T> gj = row_cell(j);
+    const T rtau = gj[3], rk = gj[4];
+    T ts[Q], fW[Q];
+#pragma unroll
+    for (int k = 0; k < Q; ++k)
+      if (lat_cy(k) != 0) {
+        const T dy = G[s][sp][k] - G[s][sm][k];
+        ts[k] = shr1(dy) + dy;
+      }
+    face<Q, NC, 0>(eq, LS[s][s0], G[s][s0], ts, cam, ca0, cap, rtau, fW);
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+      T v = FT[s][s0][k];
+      if (lat_cx(k) != 0) v = fma((T)(-lat_cx(k)) * ck, shl1(fW[k]) - fW[k], v);
+      if (lat_cy(k) != 0) v = fma((T)(-lat_cy(k)) * rk, FY[s][s0][k] - FY[s][sm][k], v);
+      o[k] = v;
+    }
+  };
+  using A = std::integral_constant<int, 0>;
+  using B = std::integral_constant<int, 1>;
+
+  const int last = y1 + 1;   // the last row that is loaded
+  auto load = [&](int slot, int r) { load_raw_buf<Q, ST>(RW[slot], Rin, plane, row_idx(r < last ? r : last)); };
+  T o[Q];
+  const bool wall_lo = GH && !per_y && y0 == 0, wall_hi = GH && !per_y && y1 == ny;
+  // prologue: the second step's rows y0 - 1 (slot 0) and y0 (slot 1), the face between them
+  if (!wall_lo) {
+    load(2, y0 - 2);
+    load(0, y0 - 1);
+    load(1, y0);
+    make_row(A{}, RW[2], y0 - 2, G[0][2], FT[0][2], false);
+    make_row(A{}, RW[0], y0 - 1, G[0][0], FT[0][0], true);
+    load(2, y0 + 1);
+    slopes(A{}, 2);
+    slopes(A{}, 0);
+    y_face(A{}, 2, 0, y0 - 1);
+    make_row(A{}, RW[1], y0, G[0][1], FT[0][1], true);
+    finish_row(A{}, 2, 0, 1, y0 - 1, o);
+    second_raw(o);
+    make_row(B{}, M, y0 - 1, G[1][0], FT[1][0], false);
+  } else {   // row -1 is a ghost in both steps
+    load(1, y0);
+    load(2, y0 + 1);
+    make_row(A{}, RW[1], -1, G[0][0], FT[0][0], false);
+    make_row(A{}, RW[1], 0, G[0][1], FT[0][1], true);
+    slopes(A{}, 0);
+    slopes(A{}, 1);
+    y_face(A{}, 0, 1, 0);
+  }
+  load(0, y0 + 2);
+  make_row(A{}, RW[2], y0 + 1, G[0][2], FT[0][2], true);
+  finish_row(A{}, 0, 1, 2, y0, o);
+  second_raw(o);
+  if (wall_lo) make_row(B{}, M, -1, G[1][0], FT[1][0], false);
+  make_row(B{}, M, y0, G[1][1], FT[1][1], true);
+  slopes(B{}, 0);
+  slopes(B{}, 1);
+  y_face(B{}, 0, 1, y0);
+
+  bool bad = false;
+  // row j of the first step, row j - 1 of the second
+  auto body = [&](int j, auto slot) {
+    constexpr int s0 = decltype(slot)::value, sp = (s0 + 1) % 3, sm = (s0 + 2) % 3;
+    load(sm, j + 2);
+    if (!(wall_hi && j == ny)) {
+      make_row(A{}, RW[sp], j + 1, G[0][sp], FT[0][sp], true);
+      finish_row(A{}, sm, s0, sp, j, o);
+      second_raw(o);
+    }   // else row ny is a ghost: M still holds row ny - 1
+    make_row(B{}, M, j, G[1][s0], FT[1][s0], true);
+    finish_row(B{}, sp, sm, s0, j - 1, o);
+    if (live) {
+      const unsigned idx = (unsigned)((j - 1) * pitch + c);
+      bad |= !__builtin_isfinite(o[0]);
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        if constexpr (ST == DUGKS_F64)
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, o[k]), Rout, idx * 8u,
+                                                (unsigned)k * plane * 8u, 0);
+        else
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, o[k]), Rout, idx * 4u,
+                                                (unsigned)k * plane * 4u, 0);
+      }
+    }
+  };
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+  using S2 = std::integral_constant<int, 2>;
+  // one loop with its exits between the rows: nothing of the windows is live
+  // after it (remainder rows after an unrolled loop kept copies of both)
+  for (int j = y0 + 1;;) {
+    body(j, S2{});
+    if (++j > y1) break;
+    body(j, S0{});
+    if (++j > y1) break;
+    body(j, S1{});
+    if (++j > y1) break;
+  }
+  // updated lanes only (see step_item)
+  if (__any(bad && live) && lane == 0) atomicOr(I->flags, (unsigned)DUGKS_FLAG_NONFINITE);
+}
+
+template <int Q, int ST, int NC, bool SYM>
+__global__ __launch_bounds__((step_max_threads<ST, 0>())) __attribute__((amdgpu_waves_per_eu(Occupancy<ST, 0>::value)))
+void k_step2(const InstDev* __restrict__ insts, const WorkItem* __restrict__ items, int nitems, int parity,
+             long long step, int xcd_remap, int persistent, const long long* __restrict__ step_base) {
+  if (step_base != nullptr) step += step_base[0];
+  const int wpb = blockDim.x >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int b = xcd_remap ? xcd_logical(blockIdx.x, gridDim.x) : blockIdx.x;
+  int item = b * wpb + w;
+  const int stride = persistent ? gridDim.x * wpb : nitems;
+  for (; item < nitems; item += stride) {
+    const WorkItem it = items[item];
+    const InstDev* I = insts + it.inst;
+    // an item reads two columns and rows past its own
+    const bool wall_x = I->bcx != DUGKS_BC_PERIODIC && (it.x0 == 0 || it.x0 + kStripCols2 + 1 >= I->nx);
+    const bool wall_y = I->bcy != DUGKS_BC_PERIODIC && (it.y0 <= 1 || it.y1 + 1 >= I->ny);
+    if (wall_x || wall_y)
+      step2_item<Q, ST, NC, true, SYM>(I, it, parity, step, lane);
+    else
+      step2_item<Q, ST, NC, false, SYM>(I, it, parity, step, lane);
     if (!persistent) break;
   }
 }
@@ -1511,12 +1757,50 @@ int launch_step_q_st(const StepArgs& a, const Launch& l, void* stream, int measu
 #undef DUGKS_STEP_LAUNCH
   DUGKS_CHECK_LAUNCH();
 }
+// Two steps in one launch (binary32 / binary64 storage without a source).
+template <int Q, int ST>
+int launch_step2_q_st(const StepArgs& a, const Launch& l, void* stream) {
+  if constexpr (Stor<ST>::neq) {
+    return -1;
+  } else {
+    if (a.src) return -1;
+    const int wpb = l.waves_per_block;
+    int blocks = (a.nitems + wpb - 1) / wpb;
+    const int persistent =
+        l.schedule == DUGKS_SCHED_PERSISTENT && a.persistent_blocks > 0 && a.persistent_blocks < blocks;
+    if (persistent) blocks = a.persistent_blocks;
+    if (blocks <= 0) return 0;
+    dim3 grid(blocks), block(64 * wpb);
+#define DUGKS_STEP2_LAUNCH(NC_, SYM_)                                                                            \
+  hipLaunchKernelGGL((k_step2<Q, ST, NC_, SYM_>), grid, block, 0, S(stream), a.insts, a.items, a.nitems, a.parity, \
+                     a.step, l.xcd_remap, persistent, a.step_base)
+    if (a.sym && ST == DUGKS_F32) {
+      switch (a.ncoef) {
+        case 2: DUGKS_STEP2_LAUNCH(2, true); break;
+        case 4: DUGKS_STEP2_LAUNCH(4, true); break;
+        default: DUGKS_STEP2_LAUNCH(8, true); break;
+      }
+    } else {
+      switch (a.ncoef) {
+        case 2: DUGKS_STEP2_LAUNCH(2, false); break;
+        case 4: DUGKS_STEP2_LAUNCH(4, false); break;
+        default: DUGKS_STEP2_LAUNCH(8, false); break;
+      }
+    }
+#undef DUGKS_STEP2_LAUNCH
+    DUGKS_CHECK_LAUNCH();
+  }
+}
+template int launch_step2_q_st<9, DUGKS_PART>(const StepArgs&, const Launch&, void*);
+template int launch_step2_q_st<5, DUGKS_PART>(const StepArgs&, const Launch&, void*);
 template int launch_step_q_st<9, DUGKS_PART>(const StepArgs&, const Launch&, void*, int);
 template int launch_step_q_st<5, DUGKS_PART>(const StepArgs&, const Launch&, void*, int);
 }  // namespace dugks
 #else
 template <int Q, int ST>
 int launch_step_q_st(const StepArgs& a, const Launch& l, void* stream, int measure);
+template <int Q, int ST>
+int launch_step2_q_st(const StepArgs& a, const Launch& l, void* stream);
 
 template <int Q>
 static int launch_plain_q(const StepArgs& a, int nx, int ny, void* stream) {
@@ -1551,6 +1835,13 @@ static int launch_step_q(const StepArgs& a, const Launch& l, void* stream, int m
 
 int launch_step_fused(const StepArgs& a, const Launch& l, void* stream, int measure) {
   return a.q == 9 ? launch_step_q<9>(a, l, stream, measure) : launch_step_q<5>(a, l, stream, measure);
+}
+
+int launch_step2(const StepArgs& a, const Launch& l, void* stream) {
+  if (a.storage == DUGKS_F64)
+    return a.q == 9 ? launch_step2_q_st<9, DUGKS_F64>(a, l, stream) : launch_step2_q_st<5, DUGKS_F64>(a, l, stream);
+  if (a.storage != DUGKS_F32) return -1;
+  return a.q == 9 ? launch_step2_q_st<9, DUGKS_F32>(a, l, stream) : launch_step2_q_st<5, DUGKS_F32>(a, l, stream);
 }
 
 int launch_clear_slot(const InstDev* insts, int ninst, long long step, int which, void* stream) {
