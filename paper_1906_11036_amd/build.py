@@ -20,8 +20,8 @@ SOURCES = [os.path.join(CSRC, "dugks_kernels.hip"), os.path.join(CSRC, "dugks_ho
            os.path.join(CSRC, "dugks1d.hip")]
 # extra objects of a source: the defines of each part
 PARTS = {"dugks_kernels.hip": [[f"-DDUGKS_PART={st}"] for st in range(4)],
-         "dugks3d_kernels.hip": [[f"-DDUGKS3_Q={q}", f"-DDUGKS3_T={t}"] for q in (19, 15, 7)
-                                 for t in ("double", "float")]}
+         "dugks3d_kernels.hip": [[f"-DDUGKS3_Q={q}", f"-DDUGKS3_T={t}", f"-DDUGKS3_SRC={s}"] for q in (19, 15, 7)
+                                 for s in (1, 0) for t in ("double", "float")]}
 LD = os.environ.get("LD", "ld")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -231,9 +231,9 @@ struct dugks3_ctx {
   // LDS bytes of a block for the launch and the device limit per block
   size_t lds_bytes(const Launch3& l) const {
     // the instantiation with mirror code runs with walls, with more than four
-    // equilibrium coefficients or with a source
+    // equilibrium coefficients or with D3Q7's source
     const bool walls = p.bc[0] != DUGKS_BC_PERIODIC || p.bc[1] != DUGKS_BC_PERIODIC ||
-                       p.bc[2] != DUGKS_BC_PERIODIC || ncoef > 4 || src_n > 0;
+                       p.bc[2] != DUGKS_BC_PERIODIC || ncoef > 4 || (q == 7 && src_n > 0);
     return step3_lds_bytes(p.storage, q, walls, l, src_n > 0);
   }
   size_t lds_limit() const {

@@ -298,14 +298,15 @@ using STab = const SrcTab*;
 // The source's coefficients as polynomials in phi at cell `cell` (index of
 // [nz][ny][nx]): an at t_n (the cell's own phi), af at t_n + h (its faces)
 // (the loads of the cell's G_j, then the sums from them)
-__device__ __forceinline__ void src_load3(const Inst3* __restrict__ I, long long cell, double* g) {
+// (NT: the terms that the instantiation has room for)
+template <int NT> __device__ __forceinline__ void src_load3(const Inst3* __restrict__ I, long long cell, double* g) {
   const GPtr<const double> G = as_global(I->src_g);
   const int n = I->src_n;
 #pragma unroll
-  for (int j = 0; j < DUGKS_MAX_SRC_TERMS; ++j)
+  for (int j = 0; j < NT; ++j)
     if (j < n) g[j] = G[j * I->src_plane + cell];
 }
-__device__ __forceinline__ void src_coefs_from3(const Inst3* __restrict__ I, STab tb, const double* g,
+template <int NT> __device__ __forceinline__ void src_coefs_from3(const Inst3* __restrict__ I, STab tb, const double* g,
                                                 double* an, double* af) {
   const int n = I->src_n;
 #pragma unroll
@@ -314,7 +315,7 @@ __device__ __forceinline__ void src_coefs_from3(const Inst3* __restrict__ I, STa
   // the coefficient of its power and zero times G_j to the others (the same
   // sums; branches on the power made the compiler copy the arrays)
 #pragma unroll
-  for (int j = 0; j < DUGKS_MAX_SRC_TERMS; ++j) {
+  for (int j = 0; j < NT; ++j) {
     if (j < n) {
       const double gj = g[j];
       const int pw = I->src_pow[j];
@@ -327,11 +328,27 @@ __device__ __forceinline__ void src_coefs_from3(const Inst3* __restrict__ I, STa
     }
   }
 }
-__device__ __forceinline__ void src_cell_coefs3(const Inst3* __restrict__ I, STab tb, long long cell,
+// one of the two alone (ex: the time factors en or ef); the same sums
+template <int NT> __device__ __forceinline__ void src_coefs_at3(const Inst3* __restrict__ I, const double* ex, const double* g, double* a) {
+  const int n = I->src_n;
+#pragma unroll
+  for (int m = 0; m < 4; ++m) a[m] = 0.0;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    if (j < n) {
+      const double gj = g[j];
+      const int pw = I->src_pow[j];
+      const double e = ex[j];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) a[m] = fma(pw == m ? e : 0.0, gj, a[m]);
+    }
+  }
+}
+template <int NT> __device__ __forceinline__ void src_cell_coefs3(const Inst3* __restrict__ I, STab tb, long long cell,
                                                 double* an, double* af) {
-  double g[DUGKS_MAX_SRC_TERMS];
-  src_load3(I, cell, g);
-  src_coefs_from3(I, tb, g, an, af);
+  double g[NT];
+  src_load3<NT>(I, cell, g);
+  src_coefs_from3<NT>(I, tb, g, an, af);
 }
 
 // A face's coefficients in the storage type: each G_j interpolated linearly
@@ -872,17 +889,16 @@ template <int Q> __host__ __device__ constexpr int half_of(int k) {
 // under the wall mirrors.  D3Q15 only without walls (a z mirror moves a
 // corner between the last two): {rest, +-x}, {+-y, +-z}, {corners with
 // c_z = +1}, {corners with c_z = -1}.  Each half is two quarters.
-// Binary64 at 2 rows does the same, with its halo rows loaded into
-// registers instead of staged (the LDS holds the four-part sums instead).
+// Binary64 at 2 rows does the same.
 template <int Q, typename T, int ROWS, bool WALLS> constexpr int parts() {
   constexpr bool quarters = Q == 19 || (Q == 15 && !WALLS);
-  return (quarters && ((sizeof(T) == 4 && ROWS >= 3) || (sizeof(T) == 8 && ROWS == 2))) ? 4 : 2;
+  return (quarters && ((sizeof(T) == 4 && ROWS >= 2) || (sizeof(T) == 8 && ROWS == 2))) ? 4 : 2;
 }
-// rows of raw f~ staged in LDS: the tile's rows and its two halo rows, or,
-// with four waves a row, only the tile's rows (each wave that makes a halo
-// row loads its quarter of it into registers)
+// rows of raw f~ staged in LDS: the tile's rows and its two halo rows, or, with
+// four waves a row, none: each wave loads its quarter of its row (and of the
+// halo row that it makes) into registers, two planes ahead
 template <int Q, typename T, int ROWS, bool WALLS> constexpr int staged_rows() {
-  return parts<Q, T, ROWS, WALLS>() == 4 ? ROWS : ROWS + 2;
+  return parts<Q, T, ROWS, WALLS>() == 4 ? 0 : ROWS + 2;
 }
 template <int Q, int P> __host__ __device__ constexpr int part_of(int k) {
   if (P == 2) return half_of<Q>(k);
@@ -1005,13 +1021,12 @@ __device__ __forceinline__ void face_out_src(const Inst3* __restrict__ I, const 
   face_out_phi<Q, P, H, A>(I, E, gb, pb, lfb, out);
 }
 
-// LDS bytes of a block with ns staging slots (E coefficients aside)
-// LDS of a block with ns staging slots, the halo rows' phi sums (binary64,
-// when those rows go through registers) included
+// LDS bytes of a block with ns staging slots, the quarters' phi sums (binary64,
+// when raw f~ goes through registers) included (E coefficients aside)
 template <int Q, int ROWS, typename T, bool WALLS> constexpr int lds_p_bytes(int ns) {
   return 3 * (ROWS + 2) * Q * kLanes * (int)sizeof(T) + ns * staged_rows<Q, T, ROWS, WALLS>() * Q * kLanes * (int)sizeof(T) +
          4 * ROWS * parts<Q, T, ROWS, WALLS>() * kLanes * (int)sizeof(T) +
-         (staged_rows<Q, T, ROWS, WALLS>() == ROWS ? 2 * 4 * kLanes * 8 : 0);
+         (staged_rows<Q, T, ROWS, WALLS>() == 0 ? (ROWS + 2) * 4 * kLanes * 8 : 0);
 }
 template <int Q, int ROWS, typename T, bool WALLS> struct LdsP {
   static constexpr int W = ROWS + 2;             // LDS rows: y0-1 .. y0+ROWS
@@ -1022,23 +1037,30 @@ template <int Q, int ROWS, typename T, bool WALLS> struct LdsP {
                             : (lds_p_bytes<Q, ROWS, T, WALLS>(2) > 81920 && lds_p_bytes<Q, ROWS, T, WALLS>(1) <= 81920)
                                   ? 1
                                   : 2;
-  // E coefficients in vector registers (from LDS) with two slots
-  static constexpr bool kVecE = WD == 1 && NS == 2;
+  // E coefficients in vector registers (from LDS) with two slots or none
   static constexpr int RR = staged_rows<Q, T, ROWS, WALLS>();
-  static constexpr bool kHD = RR == ROWS;        // halo rows loaded into registers
+  static constexpr bool kReg = RR == 0;          // raw f~ loaded into registers
+  static constexpr bool kVecE = WD == 1 && (NS == 2 || kReg);
   T gsl[3][W][Q][kLanes];                        // g of plane p in slot (p - z0) mod 3
-  unsigned raw[NS][RR][Q][WD][kLanes];           // staged f~, binary64 as low and high words
+  unsigned raw[kReg ? 0 : NS][RR][Q][WD][kLanes];   // staged f~, binary64 as low and high words (none: no bytes)
   T psum[4][ROWS][parts<Q, T, ROWS, WALLS>()][kLanes];   // the parts' interface-g sums of four faces
 };
 
-// One wave: row rw of the tile, directions of half H.  With two slots plane
-// z+2 is staged into the second while plane z+1 is read from the first; one
-// slot is refilled once every wave has read it.
-template <int Q, int NC, int ROWS, typename T, int H, bool WALLS, bool SRC>
+// One wave: row rw of the tile, directions of half H.
+// Two parts a row stage raw f~ in LDS: with two slots plane z+2 is staged into
+// the second while plane z+1 is read from the first; one slot is refilled once
+// every wave has read it.  Four parts a row load it into registers, two sets:
+// plane z+3 as soon as plane z+1 has been read, so that a load has two whole
+// planes' work to arrive in (staged in LDS it had the faces of one; with the
+// loads left out, the 256^3 D3Q19 step took 0.68 instead of 0.88 ms in binary32
+// and 1.32 instead of 2.48 ms in binary64).  A cell's phi needs all parts: each
+// writes its quarter's sum to LDS before the second barrier of the plane before.
+template <int Q, int NC, int ROWS, typename T, int H, bool WALLS, int SRC>
 __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int parity,
                                             const double* __restrict__ ring, STab tb, int planes,
                                             int strips, int tiles, LdsP<Q, ROWS, T, WALLS>& L,
-                                            const float* ecoef, double (*hphi)[4][kLanes], int w, int rw,
+                                            const float* ecoef, double (*qphi)[4][kLanes], double (*afs)[ROWS + 2][4][kLanes],
+                                            int w, int rw,
                                             int blk) {
   using LP = LdsP<Q, ROWS, T, WALLS>;
   constexpr int P = parts<Q, T, ROWS, WALLS>();
@@ -1046,7 +1068,7 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
   constexpr int NW = P * ROWS;                   // waves per block
   constexpr int HX = (2 * Q + NW - 1) / NW;      // halo-row loads per wave
   constexpr unsigned ES = sizeof(T);
-  constexpr bool kVecE = LP::kVecE && NC <= 4;
+  constexpr bool kVecE = LP::kVecE && NC <= 4 && !(SRC > 0 && LP::kReg);
   const int lane = threadIdx.x & 63;
   int b = blk;   // the block within its instance
   const int sx = b % strips;
@@ -1096,12 +1118,44 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
   auto cell_index = [&](int sr, int zp) __attribute__((always_inline)) -> unsigned {
     return (unsigned)((src_index(zp, nz, bcz) * ny + sr) * pitch + scol);
   };
-  // stage plane zp: this wave's directions of its row, and its share of the
-  // two halo rows (offsets advance in a vector register)
-  T HR[LP::kHD ? Q : 1];   // raw f~ of this wave's quarter of the halo row it makes, when not staged
+  // kReg: raw f~ of this wave's quarter of its row and, for the waves of rows 0
+  // and 1, of the halo row that they make
+  T RW[LP::kReg ? 2 : 1][LP::kReg ? Q : 1], HR[LP::kReg ? 2 : 1][LP::kReg ? Q : 1];
+  auto load_part = [&](T* v, unsigned o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+      if (part_of<Q, P>(k) == H) {
+        if constexpr (WD == 2)
+          v[k] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(Rin, o, 0u, 0));
+        else
+          v[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(Rin, o, 0u, 0));
+      }
+      o += planeB;
+    }
+  };
+  auto load_plane = [&](auto sc, int zp) __attribute__((always_inline)) {
+    constexpr int S = decltype(sc)::value;
+    load_part(RW[S], cell_index(srow, zp) * ES);
+    if (rw <= 1) load_part(HR[S], cell_index(rw == 0 ? slo : shi, zp) * ES);
+  };
+  // the quarter sums of the cells' phi of a loaded plane, to LDS
+  auto phi_sums = [&](auto sc) __attribute__((always_inline)) {
+    constexpr int S = decltype(sc)::value;
+    auto sum = [&](const T* v) __attribute__((always_inline)) {
+      double q = 0.0;
+#pragma unroll
+      for (int k = 0; k < Q; ++k)
+        if (part_of<Q, P>(k) == H) q += (double)v[k];
+      return q;
+    };
+    qphi[me][H][lane] = sum(RW[S]);
+    if (rw <= 1) qphi[rw == 0 ? 0 : W - 1][H][lane] = sum(HR[S]);
+  };
+  // two parts a row: stage plane zp, this wave's directions of its row and its
+  // share of the two halo rows (offsets advance in a vector register)
   auto stage = [&](int slot, int zp) __attribute__((always_inline)) {
     unsigned o = cell_index(srow, zp) * ES;
-    const int wme = LP::kHD ? me - 1 : me;
+    const int wme = me;
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
       if (part_of<Q, P>(k) == H) {
@@ -1110,22 +1164,6 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
           __builtin_amdgcn_raw_ptr_buffer_load_lds(Rin, LDS_PTR(&L.raw[slot][wme][k][h][0]), 4, o + 4u * h, 0, 0, 0);
       }
       o += planeB;
-    }
-    if constexpr (LP::kHD) {
-      if (rw <= 1) {   // this wave's quarter of the halo row, into registers
-        unsigned oh = cell_index(rw == 0 ? slo : shi, zp) * ES;
-#pragma unroll
-        for (int k = 0; k < Q; ++k) {
-          if (part_of<Q, P>(k) == H) {
-            if constexpr (WD == 2)
-              HR[k] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(Rin, oh, 0u, 0));
-            else
-              HR[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(Rin, oh, 0u, 0));
-          }
-          oh += planeB;
-        }
-      }
-      return;
     }
     const unsigned ilo = cell_index(slo, zp) * ES, ihi = cell_index(shi, zp) * ES;
     const int j0 = w * HX;
@@ -1142,38 +1180,37 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
                                                  oh + 4u * h, 0, 0, 0);
     }
   };
-  // raw f~ of LDS row `row` (g numbering; with the halo rows in registers
-  // only the tile's rows are staged)
+  // staged raw f~ of LDS row `row`
   auto raw_at = [&](int slot, int row, int k) __attribute__((always_inline)) -> T {
-    const int rr = LP::kHD ? row - 1 : row;
     if constexpr (WD == 1)
-      return __builtin_bit_cast(float, L.raw[slot][rr][k][0][lane]);
+      return __builtin_bit_cast(float, L.raw[slot][row][k][0][lane]);
     else
-      return __builtin_bit_cast(double, (unsigned long long)L.raw[slot][rr][k][0][lane] |
-                                            ((unsigned long long)L.raw[slot][rr][k][1][lane] << 32));
+      return __builtin_bit_cast(double, (unsigned long long)L.raw[slot][row][k][0][lane] |
+                                            ((unsigned long long)L.raw[slot][row][k][1][lane] << 32));
   };
   // g = fbar+ / b1 (eq. 2.21 over b1) of this half's directions; phi (binary64) from all of them
-  // (fromreg: the raw values are the halo row's in HR)
+  // (halo: with raw f~ in registers, the halo row's values in HR)
   // yr: the row's index (-1..ny), for the Dirichlet data
   // With a source: phi solves phi = sum f~ + dt F(phi) / 2 (eq. 2.25) and g
-  // gains lambda F(phi) rho(phi); afo receives the cell's coefficients at t_n + h
-  // (from the cell's G_j in gin when given, else loaded here).
-  // binary64 with a source and four parts (two waves a SIMD) issues the
-  // loads of the source's G_j early (registers allow it there)
-  constexpr bool kPreG = SRC && sizeof(T) == 8 && P == 4;
-  auto make_g = [&](int slot, int row, bool wy, int yr, int zp, T* g, T* f, auto fromreg,
-                    double* afo, const double* gin) __attribute__((always_inline)) {
-    constexpr bool kReg = decltype(fromreg)::value;
+  // gains lambda F(phi) rho(phi); afo receives the cell's coefficients at t_n + h.
+  // With a source and raw f~ in registers, each cell's phi is solved once, by
+  // one wave (solve_cells), and reaches the parts through LDS over the quarter
+  // sums; the same wave leaves the cell's face coefficients there in binary32
+  // (kAfLds), where registers are short; in binary64, whose LDS is full, each
+  // wave forms its row's own.
+  constexpr bool kSolve = SRC > 0 && LP::kReg;
+  constexpr bool kAfLds = kSolve && sizeof(T) == 4;
+  auto make_g = [&](auto sc, int row, bool wy, int yr, int zp, T* g, T* f, auto halo,
+                    double* afo) __attribute__((always_inline)) {
+    constexpr int slot = decltype(sc)::value;
     // phi in binary64 as (q0 + q1) + (q2 + q3), qj the sum over quarter j in
-    // index order (four chains); a halo row in registers takes the quarters'
-    // sums from LDS
+    // index order (four chains), or from the quarters' sums in LDS
     double phi;
-    if constexpr (kReg) {
+    if constexpr (LP::kReg) {
 #pragma unroll
       for (int k = 0; k < Q; ++k)
-        if (part_of<Q, P>(k) == H) f[k] = HR[k];
-      const int hr = rw;   // 0: the lower halo row, 1: the upper
-      phi = (hphi[hr][0][lane] + hphi[hr][1][lane]) + (hphi[hr][2][lane] + hphi[hr][3][lane]);
+        if (part_of<Q, P>(k) == H) f[k] = decltype(halo)::value ? HR[slot][k] : RW[slot][k];
+      phi = (qphi[row][0][lane] + qphi[row][1][lane]) + (qphi[row][2][lane] + qphi[row][3][lane]);
     } else {
       double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -1185,11 +1222,13 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
       phi = (acc[0] + acc[1]) + (acc[2] + acc[3]);
     }
     double lf = 0.0;
-    if constexpr (SRC) {
+    if constexpr (kSolve) {   // solved: phi and lambda F(phi) over the first two sums
+      phi = qphi[row][0][lane];
+      lf = qphi[row][1][lane];
+    } else if constexpr (SRC > 0) {
       const long long cell = ((long long)src_index(zp, nz, bcz) * ny + src_index(yr, ny, bcy)) * nx + scol;
       double an[4];
-      if (gin) src_coefs_from3(I, tb, gin, an, afo);
-      else src_cell_coefs3(I, tb, cell, an, afo);
+      src_cell_coefs3<SRC>(I, tb, cell, an, afo);
       phi = solve_conserved3<double>(phi, 0.5 * I->dt, an, I->src_implicit != 0);
       lf = I->lambda * poly4(an, phi);
     }
@@ -1197,7 +1236,7 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
       if (part_of<Q, P>(k) != H) continue;
-      if constexpr (SRC) g[k] = fma(ra, f[k], ev(k, p) + (T)(lf * rho3<Q>(I, k, phi)));
+      if constexpr (SRC > 0) g[k] = fma(ra, f[k], ev(k, p) + (T)(lf * rho3<Q>(I, k, phi)));
       else g[k] = fma(ra, f[k], ev(k, p));
     }
     if constexpr (WALLS) {
@@ -1217,33 +1256,49 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
   };
   // g of plane zp for this wave's row (G, and f~+ in FT) and, for the waves
   // of rows 0 and 1, the halo rows; all published to slot `slot`
-  // halo rows in registers: this wave's quarter sum of the cell phi of its
-  // halo row, to LDS (the loads must have completed; a barrier before use)
-  auto halo_sums = [&]() __attribute__((always_inline)) {
-    if constexpr (LP::kHD) {
-      if (rw <= 1) {
-        double q = 0.0;
+  // Cells of a plane solved by this wave: part 0 its row's, part 3 of rows 0 and
+  // 1 the halo rows'; their G_j are loaded a phase ahead (load_gs).
+  constexpr bool kOwnS = kSolve && H == 0;
+  const bool halo_s = kSolve && H == 3 && rw <= 1;
+  double gs[SRC > 0 ? SRC : 1];     // the solved cell's G_j
+  double gown[SRC > 0 ? SRC : 1];   // this row's G_j (!kAfLds)
+  auto load_gs = [&](int zp) __attribute__((always_inline)) {
+    if constexpr (kSolve) {
+      const long long zr = (long long)src_index(zp, nz, bcz) * ny;
+      if (kOwnS || halo_s) src_load3<SRC>(I, (zr + (kOwnS ? srow : (rw == 0 ? slo : shi))) * nx + scol, gs);
+      if constexpr (!kAfLds) src_load3<SRC>(I, (zr + srow) * nx + scol, gown);
+    }
+  };
+  auto solve_cells = [&](int slot) __attribute__((always_inline)) {
+    if constexpr (kSolve) {
+      if (kOwnS || halo_s) {
+        const int row = kOwnS ? me : (rw == 0 ? 0 : W - 1);
+        double a4[4];
+        src_coefs_at3<SRC>(I, tb->en, gs, a4);
+        const double s4 = (qphi[row][0][lane] + qphi[row][1][lane]) + (qphi[row][2][lane] + qphi[row][3][lane]);
+        const double phi = solve_conserved3<double>(s4, 0.5 * I->dt, a4, I->src_implicit != 0);
+        qphi[row][0][lane] = phi;
+        qphi[row][1][lane] = I->lambda * poly4(a4, phi);
+        if constexpr (kAfLds) {
+          src_coefs_at3<SRC>(I, tb->ef, gs, a4);
 #pragma unroll
-        for (int k = 0; k < Q; ++k)
-          if (part_of<Q, P>(k) == H) q += (double)HR[k];
-        hphi[rw][H][lane] = q;
+          for (int m = 0; m < 4; ++m) afs[slot][row][m][lane] = a4[m];
+        }
       }
     }
   };
-  auto plane_g = [&](int rs, int zp, int slot, T* G, T* FT, double* AF) __attribute__((always_inline)) {
-    using Staged = std::integral_constant<bool, false>;
-    using Halo = std::integral_constant<bool, LP::kHD>;
+  // face coefficients of LDS row `row` of the plane in slot `slot`
+  auto af_row = [&](int slot, int row, double* af) __attribute__((always_inline)) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) af[m] = afs[slot][row][m][lane];
+  };
+  auto plane_g = [&](auto rs, int zp, int slot, T* G, T* FT, double* AF) __attribute__((always_inline)) {
+    using Own = std::integral_constant<bool, false>;
+    using Halo = std::integral_constant<bool, true>;
     T f[Q];
     double afx[4];   // a halo row's coefficients (not kept)
-    // binary64 with a source, four parts: the G_j of this wave's row and of
-    // its halo row are loaded before either is used
-    double gme[DUGKS_MAX_SRC_TERMS], gho[DUGKS_MAX_SRC_TERMS];
-    if constexpr (kPreG) {
-      const long long zr = (long long)src_index(zp, nz, bcz) * ny;
-      src_load3(I, (zr + src_index(r, ny, bcy)) * nx + scol, gme);
-      if (rw <= 1) src_load3(I, (zr + src_index(rw == 0 ? y0 - 1 : y1, ny, bcy)) * nx + scol, gho);
-    }
-    make_g(rs, me, wall_y, r, zp, G, f, Staged{}, AF, kPreG ? gme : nullptr);
+    if constexpr (kSolve && !kAfLds) src_coefs_at3<SRC>(I, tb->ef, gown, AF);
+    make_g(rs, me, wall_y, r, zp, G, f, Own{}, AF);
 #pragma unroll
     for (int k = 0; k < Q; ++k)
       if (part_of<Q, P>(k) == H) FT[k] = fma(kgv, G[k], (T)(-1.0 / 3.0) * f[k]);
@@ -1251,11 +1306,10 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
     if (rw <= 1) {
       T gx[Q];
       const int row = rw == 0 ? 0 : W - 1;
-      make_g(rs, row, rw == 0 ? wall_lo : wall_hi, rw == 0 ? y0 - 1 : y1, zp, gx, f, Halo{}, afx,
-             kPreG ? gho : nullptr);
+      make_g(rs, row, rw == 0 ? wall_lo : wall_hi, rw == 0 ? y0 - 1 : y1, zp, gx, f, Halo{}, afx);
       publish(slot, row, gx);
       if (ROWS == 1) {  // one row: its waves make both halo rows (always staged)
-        make_g(rs, W - 1, wall_hi, y1, zp, gx, f, Staged{}, afx, nullptr);
+        make_g(rs, W - 1, wall_hi, y1, zp, gx, f, Halo{}, afx);
         publish(slot, W - 1, gx);
       }
     }
@@ -1273,17 +1327,13 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
 
   T G0[Q], G1[Q], O[Q], FT1[Q], FZb[Q], FZt[Q];
   double AF0[4], AF1[4];   // with a source: the own row's face coefficients at planes z and z+1
-  // one part of the pipeline differs: binary32 stages plane z+2 before the
-  // first barrier of plane z (other slot), binary64 after it (same slot)
-  constexpr bool two = LP::NS == 2;
-
-  // prologue: planes z0-1 (slot 2 of g) and z0 (slot 0), plane z0+1 staged,
-  // the bottom face of plane z0
-  if constexpr (two && LP::kHD) {   // one plane of halo registers: planes one at a time
-    stage(1, z0 - 1);
-    wait_vm_all();
-    halo_sums();
-    lds_barrier();
+  // The pipeline differs by where raw f~ goes: registers (four parts); two
+  // staging slots, plane z+2 staged before the first barrier of plane z (other
+  // slot); or one, after it (same slot).
+  constexpr bool two = !LP::kReg && LP::NS == 2;
+  using R0 = std::integral_constant<int, 0>;
+  using R1 = std::integral_constant<int, 1>;
+  auto load_ecoef = [&]() __attribute__((always_inline)) {
     if constexpr (kVecE) {
 #pragma unroll
       for (int k = 0; k < Q; ++k)
@@ -1291,43 +1341,55 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
 #pragma unroll
           for (int m = 0; m < NC; ++m) ev.c[k][m] = ecoef[k * NC + m];
     }
-    plane_g(1, z0 - 1, 2, G1, FT1, AF1);
+  };
+
+  // prologue: planes z0-1 (slot 2 of g) and z0 (slot 0), planes z0+1 and, in
+  // registers, z0+2 on their way, the bottom face of plane z0
+  if constexpr (LP::kReg) {
+    load_plane(R1{}, z0 - 1);
+    load_plane(R0{}, z0);
+    load_gs(z0 - 1);
+    phi_sums(R1{});
     lds_barrier();
-    stage(0, z0);
-    wait_vm_all();
-    halo_sums();
+    load_ecoef();
+    if constexpr (kSolve) {
+      solve_cells(2);
+      lds_barrier();
+    }
+    plane_g(R1{}, z0 - 1, 2, G1, FT1, AF1);
+    load_plane(R1{}, z0 + 1);   // z1 >= z0 + 1
+    load_gs(z0);
     lds_barrier();
-    plane_g(0, z0, 0, G0, O, AF0);
+    phi_sums(R0{});
     lds_barrier();
-    stage(1, z0 + 1);   // z1 >= z0 + 1
+    if constexpr (kSolve) {
+      solve_cells(0);
+      lds_barrier();
+    }
+    plane_g(R0{}, z0, 0, G0, O, AF0);
+    load_plane(R0{}, z0 + 2 < z1 ? z0 + 2 : z1);
+    load_gs(z0 + 1);
+    lds_barrier();
   } else if constexpr (two) {
     stage(1, z0 - 1);
     stage(0, z0);
     wait_vm_all();
     lds_barrier();
-    if constexpr (kVecE) {
-#pragma unroll
-      for (int k = 0; k < Q; ++k)
-        if (part_of<Q, P>(k) == H)
-#pragma unroll
-          for (int m = 0; m < NC; ++m) ev.c[k][m] = ecoef[k * NC + m];
-    }
-    plane_g(1, z0 - 1, 2, G1, FT1, AF1);
-    plane_g(0, z0, 0, G0, O, AF0);
+    load_ecoef();
+    plane_g(R1{}, z0 - 1, 2, G1, FT1, AF1);
+    plane_g(R0{}, z0, 0, G0, O, AF0);
     lds_barrier();
     stage(1, z0 + 1);   // z1 >= z0 + 1
   } else {
     stage(0, z0 - 1);
     wait_vm_all();
-    halo_sums();
     lds_barrier();
-    plane_g(0, z0 - 1, 2, G1, FT1, AF1);
+    plane_g(R0{}, z0 - 1, 2, G1, FT1, AF1);
     lds_barrier();
     stage(0, z0);
     wait_vm_all();
-    halo_sums();
     lds_barrier();
-    plane_g(0, z0, 0, G0, O, AF0);
+    plane_g(R0{}, z0, 0, G0, O, AF0);
     lds_barrier();
     stage(0, z0 + 1);
   }
@@ -1350,24 +1412,37 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
   }
   lds_barrier();
   if (inner) {
-    if constexpr (SRC) {
+    if constexpr (SRC > 0) {
       T sa[4];
+      if constexpr (kAfLds) {
+        af_row(2, me, AF1);
+        af_row(0, me, AF0);
+      }
       src_face_coefs3<T>(AF1, AF0, (T)zg[zb * kGeo + 1], sa);
       face_out_src<Q, P, H, 2>(I, ev, gbB, total(0, sB), sa, FZb);
     } else {
       face_out<Q, P, H, 2>(I, ev, gbB, total(0, sB), FZb);
     }
   }
-  wait_vm_all();
-  halo_sums();   // plane z0+1
+  if constexpr (LP::kReg) phi_sums(R1{});   // plane z0+1
+  else wait_vm_all();
   lds_barrier();
+  if constexpr (kSolve) {
+    solve_cells(1);
+    lds_barrier();
+  }
 
   auto body = [&](int z, auto rsl) __attribute__((always_inline)) {
-    constexpr int RS = decltype(rsl)::value;   // staging slot of plane z+1
+    constexpr int RS = decltype(rsl)::value;   // register set or staging slot of plane z+1
     const int d = z - z0;
     const int s0 = d % 3, sp = (d + 1) % 3, sm = (d + 2) % 3;
-    plane_g(RS, z + 1, sp, G1, FT1, AF1);
-    if constexpr (two) {
+    using RC = std::integral_constant<int, RS>;
+    plane_g(RC{}, z + 1, sp, G1, FT1, AF1);
+    if constexpr (LP::kReg) {
+      load_plane(RC{}, z + 3 < z1 ? z + 3 : z1);   // (past the chunk: repeated, not used)
+      load_gs(z + 2 < z1 ? z + 2 : z1);
+      lds_barrier();
+    } else if constexpr (two) {
       if (z + 2 <= z1) stage(1 - RS, z + 2);
       lds_barrier();
     } else {
@@ -1375,13 +1450,14 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
       if (z + 2 <= z1) stage(0, z + 2);
     }
     T gbW[Q], gbN[Q], gbS[Q], gbT[Q], sW = 0, sN = 0, sS = 0, sT = 0;
-    // binary64 with a source, four parts: the parts that solve the north and
-    // south faces load the G_j of that neighbouring row here, so that the
-    // face work below hides the loads' latency (used after the next barrier)
-    double gpre[DUGKS_MAX_SRC_TERMS];
+    // the parts that solve the north and south faces load the G_j of that
+    // neighbouring row here, so that the face work below hides the loads (used
+    // after the next barrier)
+    constexpr bool kPreG = kSolve && !kAfLds;
+    double gpre[SRC > 0 ? SRC : 1];
     if constexpr (kPreG && (H == 1 || H == 2)) {
       if (inner)
-        src_load3(I, ((long long)src_index(z, nz, bcz) * ny + src_index(H == 1 ? r + 1 : r - 1, ny, bcy)) * nx + scol,
+        src_load3<SRC>(I, ((long long)src_index(z, nz, bcz) * ny + src_index(H == 1 ? r + 1 : r - 1, ny, bcy)) * nx + scol,
                   gpre);
     }
     if (inner) {
@@ -1444,12 +1520,12 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
       put_sum(2, sS);
       put_sum(3, sT);
     }
-    wait_vm_all();   // this wave's loads of plane z+2 (and its older stores) are done
-    if (z + 2 <= z1) halo_sums();
-    // both halves' sums and the whole staged plane z+2 are in LDS; slot sm
+    if constexpr (LP::kReg) phi_sums(std::integral_constant<int, 1 - RS>{});   // plane z+2
+    else wait_vm_all();   // this wave's loads of plane z+2 (and its older stores) are done
+    // the parts' sums and the whole staged plane z+2 are in LDS; slot sm
     // (read only above) is free for the next plane's g
     lds_barrier();
-    if constexpr (SRC) {
+    if constexpr (SRC > 0) {
       // Each part solves phi_b of 4 / P of the four faces (west, north,
       // south, top) and writes it with lambda F(phi_b) over the face's sums,
       // which only that part reads; after a barrier every part reads all
@@ -1463,6 +1539,7 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
         };
         const long long cz = (long long)src_index(z, nz, bcz) * ny;
         T sa[4], pb, lf;
+        if constexpr (kAfLds) af_row(s0, me, AF0);
         if constexpr (0 / FP == H) {
           double AFW[4];
 #pragma unroll
@@ -1473,33 +1550,37 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
         }
         if constexpr (1 / FP == H) {
           double AFN[4], an[4];
-          if constexpr (kPreG) src_coefs_from3(I, tb, gpre, an, AFN);
-          else src_cell_coefs3(I, tb, (cz + src_index(r + 1, ny, bcy)) * nx + scol, an, AFN);
+          if constexpr (kAfLds) af_row(s0, me + 1, AFN);
+          else if constexpr (kPreG) src_coefs_at3<SRC>(I, tb->ef, gpre, AFN);
+          else src_cell_coefs3<SRC>(I, tb, (cz + src_index(r + 1, ny, bcy)) * nx + scol, an, AFN);
           src_face_coefs3<T>(AF0, AFN, yN1, sa);
           face_phi_src<T>(I, total(1, sN), sa, pb, lf);
           put_phi(1, pb, lf);
         }
         if constexpr (2 / FP == H) {
           double AFS[4], an[4];
-          if constexpr (kPreG) src_coefs_from3(I, tb, gpre, an, AFS);
-          else src_cell_coefs3(I, tb, (cz + src_index(r - 1, ny, bcy)) * nx + scol, an, AFS);
+          if constexpr (kAfLds) af_row(s0, me - 1, AFS);
+          else if constexpr (kPreG) src_coefs_at3<SRC>(I, tb->ef, gpre, AFS);
+          else src_cell_coefs3<SRC>(I, tb, (cz + src_index(r - 1, ny, bcy)) * nx + scol, an, AFS);
           src_face_coefs3<T>(AFS, AF0, yS1, sa);
           face_phi_src<T>(I, total(2, sS), sa, pb, lf);
           put_phi(2, pb, lf);
         }
         if constexpr (3 / FP == H) {
+          if constexpr (kAfLds) af_row(sp, me, AF1);
           src_face_coefs3<T>(AF0, AF1, (T)zg[(z + 2) * kGeo + 1], sa);
           face_phi_src<T>(I, total(3, sT), sa, pb, lf);
           put_phi(3, pb, lf);
         }
       }
+      solve_cells(sm);   // plane z+2
       lds_barrier();
     }
     if (inner) {
       const int zi = z + 1;
       const T kz = zg[zi * kGeo + 4];
       T fW[Q], fN[Q], fS[Q];
-      if constexpr (SRC) {
+      if constexpr (SRC > 0) {
         auto pbv = [&](int face) __attribute__((always_inline)) { return L.psum[face][rw][0][lane]; };
         auto lfv = [&](int face) __attribute__((always_inline)) { return L.psum[face][rw][1][lane]; };
         face_out_phi<Q, P, H, 0>(I, ev, gbW, pbv(0), lfv(0), fW);
@@ -1544,17 +1625,15 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
       O[k] = FT1[k];
       if (ce<Q>(k, 2) != 0) FZb[k] = FZt[k];
     }
-    if constexpr (SRC) {
+    if constexpr (SRC > 0 && !kAfLds) {
 #pragma unroll
       for (int m = 0; m < 4; ++m) AF0[m] = AF1[m];
     }
   };
-  using R0 = std::integral_constant<int, 0>;
-  using R1 = std::integral_constant<int, 1>;
   int z = z0;
-  if constexpr (two) {
+  if constexpr (two || LP::kReg) {
     for (; z + 2 <= z1; z += 2) {
-      body(z, R1{});       // (z - z0) even: plane z+1 is in slot 1
+      body(z, R1{});       // (z - z0) even: plane z+1 is in set or slot 1
       body(z + 1, R0{});
     }
     if (z < z1) body(z, R1{});
@@ -1565,7 +1644,7 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
 
 // WALLS = false: every axis periodic, no mirror code
 // BATCH: the blocks of many instances (Batch3) in one launch
-template <int Q, int NC, int ROWS, typename T, bool WALLS, bool SRC, bool BATCH>
+template <int Q, int NC, int ROWS, typename T, bool WALLS, int SRC, bool BATCH>
 __global__ __launch_bounds__((64 * parts<Q, T, ROWS, WALLS>() * ROWS)) void k_step3p(const Inst3* __restrict__ I, int parity,
                                                                        const double* __restrict__ ring,
                                                                        const SrcTab st, int planes, int strips,
@@ -1600,18 +1679,23 @@ __global__ __launch_bounds__((64 * parts<Q, T, ROWS, WALLS>() * ROWS)) void k_st
   }
   const STab tb = &st;
   double (*hp)[4][kLanes] = nullptr;
-  if constexpr (LdsP<Q, ROWS, T, WALLS>::kHD) {
-    __shared__ double hphi[2][4][kLanes];   // quarter sums of the cell phi of the two halo rows
-    hp = hphi;
+  if constexpr (LdsP<Q, ROWS, T, WALLS>::kReg) {
+    __shared__ double qphi[ROWS + 2][4][kLanes];   // quarter sums of the cells' phi of a plane's rows
+    hp = qphi;
+  }
+  double (*afs)[ROWS + 2][4][kLanes] = nullptr;
+  if constexpr (SRC > 0 && LdsP<Q, ROWS, T, WALLS>::kReg && sizeof(T) == 4) {
+    __shared__ double af[3][ROWS + 2][4][kLanes];   // the cells' face coefficients of three planes
+    afs = af;
   }
   switch (part) {
-    case 0: step3p_half<Q, NC, ROWS, T, 0, WALLS, SRC>(I, parity, ring, tb, planes, strips, tiles, L, ec, hp, w, rw, blk); break;
-    case 1: step3p_half<Q, NC, ROWS, T, 1, WALLS, SRC>(I, parity, ring, tb, planes, strips, tiles, L, ec, hp, w, rw, blk); break;
+    case 0: step3p_half<Q, NC, ROWS, T, 0, WALLS, SRC>(I, parity, ring, tb, planes, strips, tiles, L, ec, hp, afs, w, rw, blk); break;
+    case 1: step3p_half<Q, NC, ROWS, T, 1, WALLS, SRC>(I, parity, ring, tb, planes, strips, tiles, L, ec, hp, afs, w, rw, blk); break;
     case 2:
-      if constexpr (P > 2) step3p_half<Q, NC, ROWS, T, 2, WALLS, SRC>(I, parity, ring, tb, planes, strips, tiles, L, ec, hp, w, rw, blk);
+      if constexpr (P > 2) step3p_half<Q, NC, ROWS, T, 2, WALLS, SRC>(I, parity, ring, tb, planes, strips, tiles, L, ec, hp, afs, w, rw, blk);
       break;
     default:
-      if constexpr (P > 2) step3p_half<Q, NC, ROWS, T, 3, WALLS, SRC>(I, parity, ring, tb, planes, strips, tiles, L, ec, hp, w, rw, blk);
+      if constexpr (P > 2) step3p_half<Q, NC, ROWS, T, 3, WALLS, SRC>(I, parity, ring, tb, planes, strips, tiles, L, ec, hp, afs, w, rw, blk);
       break;
   }
 }
@@ -1766,10 +1850,10 @@ static inline hipStream_t S(void* s) { return (hipStream_t)s; }
 static size_t step3h_lds_bytes(int q, const Launch3& l) { return (size_t)3 * (l.rows + 2) * q * kLanes * 8; }
 
 // The step kernels are compiled apart from the rest of this file, one object
-// per lattice and storage type (DUGKS3_Q, DUGKS3_T), so that a build runs them
-// in parallel.
+// per lattice, storage type and whether they take a source (DUGKS3_Q,
+// DUGKS3_T, DUGKS3_SRC), so that a build runs them in parallel.
 struct Args3;
-template <int Q, typename T>
+template <int Q, typename T, bool SRC>
 int step3_qt(const Args3& a, const Inst3& h, bool walls, long long blocks, const Launch3& l, void* stream);
 
 // The launch arguments of the staged kernel
@@ -1813,12 +1897,12 @@ static void step3_row_waves(const Inst3* d, const Inst3& h, int parity, const do
   }
 }
 
-template <int Q, int NC, int ROWS, typename T, bool WALLS, bool SRC, bool BATCH>
+template <int Q, int NC, int ROWS, typename T, bool WALLS, int SRC, bool BATCH>
 static void step3p_go(const Args3& a, const Launch3& l, dim3 grid, hipStream_t st) {
   hipLaunchKernelGGL((k_step3p<Q, NC, ROWS, T, WALLS, SRC, BATCH>), grid, dim3(64 * parts<Q, T, ROWS, WALLS>() * ROWS),
                      0, st, a.d, a.parity, a.ring, a.ss, l.planes, a.strips, a.tiles, a.bt);
 }
-template <int Q, int NC, typename T, bool WALLS, bool SRC, bool BATCH = false>
+template <int Q, int NC, typename T, bool WALLS, int SRC, bool BATCH = false>
 static void step3p_launch(const Args3& a, const Launch3& l, dim3 grid, hipStream_t st) {
   if constexpr (sizeof(T) == 8) {   // rows 1 and 2 fit the LDS
     if (l.rows == 1) step3p_go<Q, NC, 1, T, WALLS, SRC, BATCH>(a, l, grid, st);
@@ -1831,39 +1915,43 @@ static void step3p_launch(const Args3& a, const Launch3& l, dim3 grid, hipStream
     }
   }
 }
-// With a source: the instantiation with mirror code (it serves periodic axes too)
-template <int Q, int NC, typename T>
-static void step3p_rows(const Args3& a, const Inst3& h, bool walls, const Launch3& l, dim3 grid, hipStream_t st) {
-  if (a.bt.insts != nullptr) {   // a batch
-    if (NC == 8 || walls) step3p_launch<Q, NC, T, true, false, true>(a, l, grid, st);
-    else if constexpr (NC != 8) step3p_launch<Q, NC, T, false, false, true>(a, l, grid, st);
-  } else if (h.src_n > 0) step3p_launch<Q, NC, T, true, true>(a, l, grid, st);
-  else if (NC == 8 || walls) step3p_launch<Q, NC, T, true, false>(a, l, grid, st);
-  else if constexpr (NC != 8) step3p_launch<Q, NC, T, false, false>(a, l, grid, st);
-}
-
-template <int Q, int NC, typename T>
+template <int Q, int NC, typename T, bool SRC>
 static void step3_nc(const Args3& a, const Inst3& h, bool walls, const Launch3& l, dim3 grid, hipStream_t st) {
-  if constexpr (Q != 7)   // split directions
-    step3p_rows<Q, NC, T>(a, h, walls, l, grid, st);
-  else if (h.src_n > 0)   // D3Q7 with a source: the staged kernel, two parts a row
-    step3p_launch<Q, NC, T, true, true>(a, l, grid, st);
-  else                    // D3Q7: a whole row per wave
+  constexpr int kAny = DUGKS_MAX_SRC_TERMS;
+  if constexpr (SRC && (Q == 7 || NC == 8)) {   // D3Q7 with a source: the staged kernel, two parts a row
+    step3p_launch<Q, NC, T, true, kAny>(a, l, grid, st);
+  } else if constexpr (SRC) {
+    // up to two terms (registers for fewer G_j; binary32 spills with six), or any number
+    if (walls && h.src_n <= 2) step3p_launch<Q, NC, T, true, 2>(a, l, grid, st);
+    else if (walls) step3p_launch<Q, NC, T, true, kAny>(a, l, grid, st);
+    else if (h.src_n <= 2) step3p_launch<Q, NC, T, false, 2>(a, l, grid, st);
+    else step3p_launch<Q, NC, T, false, kAny>(a, l, grid, st);
+  } else if constexpr (Q == 7) {   // D3Q7: a whole row per wave
     step3_row_waves<Q, NC, T>(a.d, h, a.parity, a.ring, l, a.strips, a.tiles, grid, st);
+  } else {
+    const bool batch = a.bt.insts != nullptr;
+    if (NC == 8 || walls) {
+      if (batch) step3p_launch<Q, NC, T, true, 0, true>(a, l, grid, st);
+      else step3p_launch<Q, NC, T, true, 0>(a, l, grid, st);
+    } else if constexpr (NC != 8) {
+      if (batch) step3p_launch<Q, NC, T, false, 0, true>(a, l, grid, st);
+      else step3p_launch<Q, NC, T, false, 0>(a, l, grid, st);
+    }
+  }
 }
 
-template <int Q, typename T>
+template <int Q, typename T, bool SRC>
 int step3_qt(const Args3& a, const Inst3& h, bool walls, long long blocks, const Launch3& l, void* stream) {
   if (blocks <= 0 || blocks > 0x7fffffffLL) return -1;
   const dim3 grid((unsigned)blocks);
   switch (h.ncoef <= 2 ? 2 : (h.ncoef <= 4 ? 4 : 8)) {
-    case 2: step3_nc<Q, 2, T>(a, h, walls, l, grid, S(stream)); break;
-    case 4: step3_nc<Q, 4, T>(a, h, walls, l, grid, S(stream)); break;
-    default: step3_nc<Q, 8, T>(a, h, walls, l, grid, S(stream)); break;
+    case 2: step3_nc<Q, 2, T, SRC>(a, h, walls, l, grid, S(stream)); break;
+    case 4: step3_nc<Q, 4, T, SRC>(a, h, walls, l, grid, S(stream)); break;
+    default: step3_nc<Q, 8, T, SRC>(a, h, walls, l, grid, S(stream)); break;
   }
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
-template int step3_qt<DUGKS3_Q, DUGKS3_T>(const Args3&, const Inst3&, bool, long long, const Launch3&, void*);
+template int step3_qt<DUGKS3_Q, DUGKS3_T, (DUGKS3_SRC != 0)>(const Args3&, const Inst3&, bool, long long, const Launch3&, void*);
 }  // namespace dugks3
 #else
 long long step3_blocks(const Inst3& h, const Launch3& l) {
@@ -1873,10 +1961,15 @@ long long step3_blocks(const Inst3& h, const Launch3& l) {
   return strips * tiles * chunks;
 }
 
+template <int Q, typename T>
+static int step3_src(const Args3& a, const Inst3& h, bool walls, long long blocks, const Launch3& l, void* stream) {
+  return h.src_n > 0 ? step3_qt<Q, T, true>(a, h, walls, blocks, l, stream)
+                     : step3_qt<Q, T, false>(a, h, walls, blocks, l, stream);
+}
 template <int Q>
 static int step3_q(const Args3& a, const Inst3& h, bool walls, long long blocks, const Launch3& l, void* stream) {
-  return h.storage == DUGKS_F64 ? step3_qt<Q, double>(a, h, walls, blocks, l, stream)
-                                : step3_qt<Q, float>(a, h, walls, blocks, l, stream);
+  return h.storage == DUGKS_F64 ? step3_src<Q, double>(a, h, walls, blocks, l, stream)
+                                : step3_src<Q, float>(a, h, walls, blocks, l, stream);
 }
 
 int launch_step3(const Inst3* d, const Inst3& h, int parity, long long step, const Launch3& l, void* stream) {
@@ -1919,11 +2012,12 @@ size_t step3_lds_bytes(int storage, int q, bool walls, const Launch3& l, bool sr
   const size_t e = storage == DUGKS_F64 ? 8 : 4;
   // parts<Q, T, ROWS, WALLS>(), walls meaning the instantiation with mirror code
   const bool quarters = q == 19 || (q == 15 && !walls);
-  const size_t np = (quarters && ((storage != DUGKS_F64 && l.rows >= 3) || (storage == DUGKS_F64 && l.rows == 2))) ? 4 : 2;
-  const size_t rr = np == 4 ? l.rows : l.rows + 2;   // staged_rows<>()
-  const size_t hs = rr == (size_t)l.rows ? (size_t)2 * 4 * kLanes * 8 : 0;        // halo rows' phi sums
+  const size_t np = (quarters && ((storage != DUGKS_F64 && l.rows >= 2) || (storage == DUGKS_F64 && l.rows == 2))) ? 4 : 2;
+  const size_t rr = np == 4 ? 0 : l.rows + 2;   // staged_rows<>()
+  const size_t as = src && np == 4 && e == 4 ? (size_t)3 * (l.rows + 2) * 4 * kLanes * 8 : 0;   // face coefficients
+  const size_t hs = rr == 0 ? (size_t)(l.rows + 2) * 4 * kLanes * 8 : 0;        // quarters' phi sums
   auto bytes = [&](size_t ns) {
-    return 3 * (l.rows + 2) * q * kLanes * e + ns * rr * q * kLanes * e + (size_t)4 * l.rows * np * kLanes * e + hs;
+    return as + 3 * (l.rows + 2) * q * kLanes * e + ns * rr * q * kLanes * e + (size_t)4 * l.rows * np * kLanes * e + hs;
   };
   if (storage == DUGKS_F64) return bytes(1);
   return (bytes(2) > 81920 && bytes(1) <= 81920) ? bytes(1) : bytes(2);
