@@ -15,10 +15,11 @@
 // In one dimension E_0 = phi (3 - d)/3 and E_{+-} = phi (d +- 3 b / c)/6, and
 // R_0 = 0, R_{+-} = +- dB/dt / (2c).
 //
-// Fused step kernel: a wave owns 62 consecutive cells (64 lanes, one halo
-// lane each side), loads f~ and phi^{n-1} of its 64 cells, forms fbar+, f~+
-// and dB/dt per lane, computes the west face of every lane (the east face is
-// the next lane's west face, by DPP) and stores f~ and phi^n.  No LDS.
+// Fused step kernel: a wave owns 64 - 2 NS consecutive cells (NS halo lanes
+// each side for NS steps), loads f~ and phi^{n-1} of its 64 cells, and for each
+// step forms fbar+, f~+ and dB/dt per lane and computes the west face of every
+// lane (the east face is the next lane's west face, by DPP); it stores f~ and
+// phi^n of the last step.  No LDS.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -31,7 +32,7 @@
 
 namespace dugks1 {
 
-constexpr int kCols = 62;
+constexpr int kMultiSteps = 4;       // steps of a launch in a run of so many
 constexpr int kWavesPerBlock = 16;   // large blocks: fewer block dispatches for a streaming kernel
 constexpr int kRedThreads = 256;
 constexpr int kRedBlocks = 2048;   // 8 blocks a CU: a reduction streams (512 left it at 2.9 TB/s)
@@ -89,80 +90,120 @@ __device__ __forceinline__ void feq1(T phi, T b, T d, T c3, T* E) {
   E[2] = phi * (d - c3 * b) * (T)(1.0 / 6.0);
 }
 
-template <typename T, bool UNI>
-__global__ __launch_bounds__(64 * kWavesPerBlock) void k_step1(const Inst1<T> I, const Step1<T> S) {
+// The steps of one launch.
+template <typename T, int NS> struct Steps1 { Step1<T> s[NS]; };
+
+// NS steps in one launch: a wave reads its 64 cells once, takes the steps in
+// registers, each eating one lane at either end, and writes 64 - 2 NS cells.
+// The result of a step is rounded to the storage type as a store would, so NS
+// does not change it.  One step a launch streams the state (5.4 TB/s); four
+// (kMultiSteps) leave a quarter of the bytes a step and the arithmetic to bound
+// it: 2^24 cells binary32 98 -> @@ us a step.
+template <typename T, bool UNI, int NS>
+__global__ __launch_bounds__(64 * kWavesPerBlock) void k_step1(const Inst1<T> I, const Steps1<T, NS> SS) {
   const int lane = threadIdx.x & 63;
   const int wv = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int nx = I.nx, pitch = I.pitch;
-  const int x0 = wv * kCols;
+  constexpr int kLive = 64 - 2 * NS;
+  const int x0 = wv * kLive;
   if (x0 >= nx) return;                  // whole wave: no cell of this strip exists
-  const int c = x0 - 1 + lane;           // this lane's cell (-1 and nx are ghosts)
+  const int c = x0 - NS + lane;          // this lane's cell (-1 and nx are ghosts)
   const bool periodic = I.bc == DUGKS_BC_PERIODIC;
+  // the cell whose values the lane holds: itself, the cell it wraps to, or the
+  // cell next to the wall (lanes further out than a result reaches: any cell)
   int src = c;
-  if (c < 0) src = periodic ? nx - 1 : 0;
-  else if (c >= nx) src = periodic ? (c - nx < nx ? c - nx : nx - 1) : nx - 1;
+  if (periodic) {
+    if (NS == 1) {
+      if (c < 0) src = nx - 1;
+      else if (c >= nx) src = c - nx < nx ? c - nx : nx - 1;
+    } else {
+      const int d = c < nx + NS ? c : nx + NS - 1;
+      src = d % nx;
+      src = src < 0 ? src + nx : src;
+    }
+  } else {
+    src = c < 0 ? 0 : (c >= nx ? nx - 1 : c);
+  }
   const bool ghost = !periodic && (c < 0 || c >= nx);
 
   T f[3];
 #pragma unroll
   for (int i = 0; i < 3; ++i) f[i] = I.in[(size_t)i * pitch + src];
-  const T pp = I.in[(size_t)3 * pitch + src];
-  const double phid = (double)f[0] + (double)f[1] + (double)f[2];   // phi = sum f~ (binary64)
-  const T phi = (T)phid;
+  T pp = I.in[(size_t)3 * pitch + src];
   const T x = UNI ? (T)(I.x0 + ((double)src + 0.5) * I.w) : (T)I.xc[src + 1];
-  const T dB = ((S.pn * x + S.qn) * phi - (S.pm * x + S.qm) * pp) * I.inv_dt;
-  T E[3], g[3], ft[3];
-  feq1(phi, S.pn * x + S.qn, S.dn, I.c3, E);
-  const T lr = I.lambda * dB * I.half_inv_c;    // lambda R_+ (R_- = -R_+, R_0 = 0)
-  const T ES[3] = {E[0], E[1] + lr, E[2] - lr};
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    g[i] = I.a1 * f[i] + I.b1 * ES[i];          // fbar+
-    ft[i] = I.a2 * f[i] + I.b2 * ES[i];         // f~+
-  }
-  T dBl = dB;
-  if (ghost) {
-    // non-equilibrium extrapolation: fbar+_g = E(phi_g, x_g) + fbar+_a - E(phi_a, x_a)
-    const int side = c < 0 ? 0 : 1;
-    const T phg = (T)S.gcur[side], phgp = (T)S.gprev[side];
-    const T xg = UNI ? (T)(I.x0 + ((c < 0 ? -1.0 : (double)nx) + 0.5) * I.w) : (T)I.xc[c < 0 ? 0 : nx + 1];
-    T Eg[3];
-    feq1(phg, S.pn * xg + S.qn, S.dn, I.c3, Eg);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) g[i] = Eg[i] + (g[i] - E[i]);
-    dBl = ((S.pn * xg + S.qn) * phg - (S.pm * xg + S.qm) * phgp) * I.inv_dt;
-  }
-
-  // west face of this lane's cell: between lanes - 1 and lane (face index c)
-  const int m = c < 0 ? 0 : (c > nx ? nx : c);
+  // ghost centre; the face on the lane's west side (a wrapped cell's beyond the
+  // ends), its factors, and the cell's update factor
+  const T xg = UNI ? (T)(I.x0 + ((c < 0 ? -1.0 : (double)nx) + 0.5) * I.w) : (T)I.xc[c < 0 ? 0 : nx + 1];
+  const int m = periodic && (c < 0 || c > nx) ? src : (c < 0 ? 0 : (c > nx ? nx : c));
   const T am = UNI ? I.uam : I.face[(size_t)m * 3 + 0];
   const T a0 = UNI ? I.ua0 : I.face[(size_t)m * 3 + 1];
   const T ap = UNI ? I.uap : I.face[(size_t)m * 3 + 2];
-  T fb[3];
-  {
-    const T L0 = shr1(g[0]), L1 = shr1(g[1]), L2 = shr1(g[2]), dL = shr1(dBl);
-    fb[0] = L0 + a0 * (g[0] - L0);
-    fb[1] = L1 + ap * (g[1] - L1);     // c_i = +c
-    fb[2] = L2 + am * (g[2] - L2);     // c_i = -c
-    const T phib = (T)((double)fb[0] + (double)fb[1] + (double)fb[2]);
-    const T dBb = dL + a0 * (dBl - dL);
-    const T xb = UNI ? (T)(I.x0 + (double)m * I.w) : (T)I.xf[m];
-    T Eb[3];
-    feq1(phib, S.ph * xb + S.qh, S.dh, I.c3, Eb);
-    const T lrb = I.lambda * dBb * I.half_inv_c;
-    fb[1] = I.a3 * fb[1] + I.b3 * (Eb[1] + lrb);
-    fb[2] = I.a3 * fb[2] + I.b3 * (Eb[2] - lrb);
+  const T xb = UNI ? (T)(I.x0 + (double)m * I.w) : (T)I.xf[m];
+  const T u = ghost ? (T)0 : (UNI ? I.uupd : I.upd[src]);
+
+#pragma unroll
+  for (int st = 0; st < NS; ++st) {
+    const Step1<T>& S = SS.s[st];
+    const double phid = (double)f[0] + (double)f[1] + (double)f[2];   // phi = sum f~ (binary64)
+    const T phi = (T)phid;
+    const T dB = ((S.pn * x + S.qn) * phi - (S.pm * x + S.qm) * pp) * I.inv_dt;
+    T E[3], g[3], ft[3];
+    feq1(phi, S.pn * x + S.qn, S.dn, I.c3, E);
+    const T lr = I.lambda * dB * I.half_inv_c;    // lambda R_+ (R_- = -R_+, R_0 = 0)
+    const T ES[3] = {E[0], E[1] + lr, E[2] - lr};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      g[i] = I.a1 * f[i] + I.b1 * ES[i];          // fbar+
+      ft[i] = I.a2 * f[i] + I.b2 * ES[i];         // f~+
+    }
+    T dBl = dB;
+    if (ghost) {
+      // non-equilibrium extrapolation: fbar+_g = E(phi_g, x_g) + fbar+_a - E(phi_a, x_a)
+      const int side = c < 0 ? 0 : 1;
+      const T phg = (T)S.gcur[side], phgp = (T)S.gprev[side];
+      T Eg[3];
+      feq1(phg, S.pn * xg + S.qn, S.dn, I.c3, Eg);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) g[i] = Eg[i] + (g[i] - E[i]);
+      dBl = ((S.pn * xg + S.qn) * phg - (S.pm * xg + S.qm) * phgp) * I.inv_dt;
+    }
+
+    // west face of this lane's cell: between lanes - 1 and lane (face index c)
+    T fb[3];
+    {
+      const T L0 = shr1(g[0]), L1 = shr1(g[1]), L2 = shr1(g[2]), dL = shr1(dBl);
+      fb[0] = L0 + a0 * (g[0] - L0);
+      fb[1] = L1 + ap * (g[1] - L1);     // c_i = +c
+      fb[2] = L2 + am * (g[2] - L2);     // c_i = -c
+      const T phib = (T)((double)fb[0] + (double)fb[1] + (double)fb[2]);
+      const T dBb = dL + a0 * (dBl - dL);
+      T Eb[3];
+      feq1(phib, S.ph * xb + S.qh, S.dh, I.c3, Eb);
+      const T lrb = I.lambda * dBb * I.half_inv_c;
+      fb[1] = I.a3 * fb[1] + I.b3 * (Eb[1] + lrb);
+      fb[2] = I.a3 * fb[2] + I.b3 * (Eb[2] - lrb);
+    }
+    // flux difference (eq. 2.9): c (f_E - f_W) for +c, -c (f_E - f_W) for -c
+    f[0] = ft[0];
+    f[1] = ft[1] - u * (shl1(fb[1]) - fb[1]);
+    f[2] = ft[2] + u * (shl1(fb[2]) - fb[2]);
+    pp = phi;
+    if (st + 1 < NS && !periodic) {   // a ghost lane holds the cell next to the wall
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const T e = shl1(f[i]), w = shr1(f[i]);
+        f[i] = c < 0 ? e : (c >= nx ? w : f[i]);
+      }
+      const T e = shl1(pp), w = shr1(pp);
+      pp = c < 0 ? e : (c >= nx ? w : pp);
+    }
   }
-  // flux difference (eq. 2.9): c (f_E - f_W) for +c, -c (f_E - f_W) for -c
-  const T u = c >= 0 && c < nx ? (UNI ? I.uupd : I.upd[c]) : (T)0;
-  const T o1 = ft[1] - u * (shl1(fb[1]) - fb[1]);
-  const T o2 = ft[2] + u * (shl1(fb[2]) - fb[2]);
-  if (lane >= 1 && lane <= kCols && c < nx) {
+  if (lane >= NS && lane < NS + kLive && c < nx) {
     T* o = I.out;
-    o[c] = ft[0];
-    o[(size_t)pitch + c] = o1;
-    o[(size_t)2 * pitch + c] = o2;
-    o[(size_t)3 * pitch + c] = phi;
+    o[c] = f[0];
+    o[(size_t)pitch + c] = f[1];
+    o[(size_t)2 * pitch + c] = f[2];
+    o[(size_t)3 * pitch + c] = pp;
   }
 }
 
@@ -338,24 +379,29 @@ struct dugks1_ctx {
 
 static hipStream_t S1(const dugks1_ctx* x) { return x->stream; }
 
-template <typename T> static void launch_step(dugks1_ctx* x) {
-  const double tn = x->time(), tm = tn - x->dt, th = tn + x->h;
-  Step1<T> S{};
-  S.pn = (T)x->bcoef_p(tn); S.qn = (T)x->bcoef_q(tn); S.dn = (T)x->dcoef(tn);
-  S.pm = (T)x->bcoef_p(tm); S.qm = (T)x->bcoef_q(tm);
-  S.ph = (T)x->bcoef_p(th); S.qh = (T)x->bcoef_q(th); S.dh = (T)x->dcoef(th);
-  if (x->p.bc == DUGKS_BC_DIRICHLET) {
-    S.gcur = x->ghosts + 2 * (size_t)x->ghosts_pos;
-    if (!x->have_gprev) S.gprev = S.gcur;
-    else if (x->ghosts_pos > 0) S.gprev = S.gcur - 2;
-    else S.gprev = (const double*)(x->ws + x->off_gslot);
+// NS steps from the current one in one launch
+template <typename T, int NS> static void launch_steps(const dugks1_ctx* x) {
+  Steps1<T, NS> SS{};
+  for (int k = 0; k < NS; ++k) {
+    Step1<T>& S = SS.s[k];
+    const double tn = x->p.t0 + (double)(x->steps + k) * x->dt, tm = tn - x->dt, th = tn + x->h;
+    S.pn = (T)x->bcoef_p(tn); S.qn = (T)x->bcoef_q(tn); S.dn = (T)x->dcoef(tn);
+    S.pm = (T)x->bcoef_p(tm); S.qm = (T)x->bcoef_q(tm);
+    S.ph = (T)x->bcoef_p(th); S.qh = (T)x->bcoef_q(th); S.dh = (T)x->dcoef(th);
+    if (x->p.bc == DUGKS_BC_DIRICHLET) {
+      const int pos = x->ghosts_pos + k;
+      S.gcur = x->ghosts + 2 * (size_t)pos;
+      if (!x->have_gprev && k == 0) S.gprev = S.gcur;
+      else if (pos > 0) S.gprev = S.gcur - 2;
+      else S.gprev = (const double*)(x->ws + x->off_gslot);
+    }
   }
-  const long long waves = (x->nx + kCols - 1) / kCols;
+  const long long waves = (x->nx + 64 - 2 * NS - 1) / (64 - 2 * NS);
   const dim3 grid((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock)), block(64 * kWavesPerBlock);
   if (x->uniform)
-    hipLaunchKernelGGL((k_step1<T, true>), grid, block, 0, S1(x), x->inst<T>(x->parity), S);
+    hipLaunchKernelGGL((k_step1<T, true, NS>), grid, block, 0, S1(x), x->inst<T>(x->parity), SS);
   else
-    hipLaunchKernelGGL((k_step1<T, false>), grid, block, 0, S1(x), x->inst<T>(x->parity), S);
+    hipLaunchKernelGGL((k_step1<T, false, NS>), grid, block, 0, S1(x), x->inst<T>(x->parity), SS);
 }
 
 extern "C" {
@@ -590,15 +636,17 @@ int dugks1_step(dugks1_ctx* x, int nsteps) {
   if (nsteps < 0) return x->fail(DUGKS_E_ARG, "nsteps must be >= 0");
   if (x->p.bc == DUGKS_BC_DIRICHLET && x->ghosts_n - x->ghosts_pos < nsteps)
     return x->fail(DUGKS_E_STATE, "Dirichlet data exhausted: supply more with dugks1_set_dirichlet");
-  for (int s = 0; s < nsteps; ++s) {
-    if (x->p.storage == DUGKS_F64) launch_step<double>(x);
-    else launch_step<float>(x);
+  for (int left = nsteps; left > 0;) {
+    const int n = left >= kMultiSteps ? kMultiSteps : 1;
+    if (x->p.storage == DUGKS_F64) n == 1 ? launch_steps<double, 1>(x) : launch_steps<double, kMultiSteps>(x);
+    else n == 1 ? launch_steps<float, 1>(x) : launch_steps<float, kMultiSteps>(x);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return x->hipfail(e, "step launch");
     x->parity ^= 1;
-    x->steps += 1;
-    if (x->p.bc == DUGKS_BC_DIRICHLET) x->ghosts_pos += 1;
+    x->steps += n;
+    if (x->p.bc == DUGKS_BC_DIRICHLET) x->ghosts_pos += n;
     x->have_gprev = true;
+    left -= n;
   }
   return DUGKS_OK;
 }

@@ -150,3 +150,27 @@ def test_full_size_one_step_sampled_1d(storage, tol):
     err = float(np.abs(gpu[:, cells].T - ref).max() / np.abs(ref).max())
     say(f"  sampled max rel err {err:.2e} over {len(cells)} cells")
     assert err <= tol
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 8, 55, 56, 57, 59, 60, 61, 64, 112, 113, 900])
+@pytest.mark.parametrize("bc", [P, D])
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_four_steps_a_launch(n, bc, storage):
+    """Runs of four or more steps take four a launch (56 cells a wave): bit for bit
+    the steps taken one by one on uniform meshes (meshes of fewer cells than a
+    wave's halo and the edges of its strips among them)."""
+    p = W.random_problem1d(950 + n, n, bc=bc)
+    say(f"case 1d four steps n={n} bc={bc} {storage}")
+    a, e = dg.Solver1D(p, storage), dg.Solver1D(p, storage)
+    for s in (a, e):
+        s.set_phi(p.phi0)
+    for steps in (9, 4, 6):
+        if bc == D:
+            g = a.ghost_table(steps)
+            for s in (a, e):
+                s.set_dirichlet(g)
+        a.step(steps, auto_ghosts=False)
+        for _ in range(steps):
+            e.step(1, auto_ghosts=False)
+        assert np.array_equal(a.get_f(), e.get_f())
+        assert np.array_equal(a.get_phi_prev(), e.get_phi_prev())
