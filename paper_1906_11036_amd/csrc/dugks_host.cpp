@@ -25,6 +25,7 @@ static constexpr uint32_t kMagicBatch = 0x44554742u;  // "DUGB"
 // multiples of 4, the period of the buffer parity and the 16-bit scale slots.
 static constexpr int kGraphSteps[2] = {32, 4};
 
+static constexpr int kSlots = 4 * kSlotWays;
 static constexpr int kRedOut = 9;   // values of a reduction's result (launch_reduce_widths)
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -354,7 +355,7 @@ struct Engine {
       in.off_colgeo_f = off; off += align256(sizeof(float) * in.colgeo_f.size());
       in.off_rowgeo_f = off; off += align256(sizeof(float) * in.rowgeo_f.size());
       in.off_widths = off; off += align256(sizeof(double) * in.widths.size());
-      in.off_slots = off; off += align256(sizeof(float) * 4);
+      in.off_slots = off; off += align256(sizeof(float) * kSlots);
       in.off_flags = off; off += align256(sizeof(unsigned));
     }
     total_bytes = off;
@@ -389,7 +390,7 @@ struct Engine {
   int default_rows() const {
     const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48};
     const bool two = two_steps_ok();
-    const double v = (storage == DUGKS_F64 || any_source()) ? 1.0 : 0.75, c = two ? 3.5 : (neq() ? 1.5 : 2.5);
+    const double v = (storage == DUGKS_F64 || any_source()) ? 1.0 : 0.75, c = two ? 3.5 : 2.5;
     const int cols = two ? kStripCols2 : kStripCols;
     double best_cost = 0;
     int best = 0;
@@ -551,7 +552,7 @@ struct Engine {
     if (rc) return rc;
     for (auto& in : inst) {
       rc = launch_fill_u32((unsigned*)(ws + in.off_flags), 0u, 1, stream);
-      if (rc == 0) rc = launch_fill_u32((unsigned*)(ws + in.off_slots), 0u, 4, stream);
+      if (rc == 0) rc = launch_fill_u32((unsigned*)(ws + in.off_slots), 0u, kSlots, stream);
       if (rc) return fail(DUGKS_E_HIP, "clear flags");
     }
     return DUGKS_OK;
@@ -638,10 +639,6 @@ struct Engine {
       a.nitems = (int)items2.size();
       rc = launch_step2(a, launch, s);
     } else {
-      if (neq()) {
-        rc = launch_clear_slot(dev_table(), (int)inst.size(), n, measure ? 3 : 0, s);
-        if (rc) return fail(DUGKS_E_HIP, "clear slot launch failed");
-      }
       rc = launch_step_fused(a, launch, s, measure ? 1 : 0);
     }
     if (rc) return fail(DUGKS_E_HIP, std::string("step launch failed: ") + hipGetErrorString(hipGetLastError()));
@@ -772,8 +769,8 @@ struct Engine {
       const float one = 1.0f;
       unsigned one_bits;
       memcpy(&one_bits, &one, sizeof(one_bits));
-      rc = launch_fill_u32((unsigned*)(ws + in.off_slots), 0u, 4, stream);
-      if (rc == 0) rc = launch_fill_u32((unsigned*)(ws + in.off_slots) + 2, one_bits, 1, stream);
+      rc = launch_fill_u32((unsigned*)(ws + in.off_slots), 0u, kSlots, stream);
+      if (rc == 0) rc = launch_fill_u32((unsigned*)(ws + in.off_slots) + 2 * kSlotWays, one_bits, 1, stream);
     }
     if (rc == 0) rc = launch_fill_u32((unsigned*)(ws + in.off_flags), 0u, 1, stream);
     e = hipStreamSynchronize(stream);
@@ -800,7 +797,7 @@ struct Engine {
       if (e != hipSuccess) { (void)hipFree(tmp); return hipfail(e, "copy f"); }
       src = tmp;
     }
-    int rc = launch_fill_u32((unsigned*)(ws + in.off_slots), 0u, 4, stream);
+    int rc = launch_fill_u32((unsigned*)(ws + in.off_slots), 0u, kSlots, stream);
     if (rc == 0 && neq()) rc = launch_set_f_pass(dev_inst(k), host_table[k], src, 0, 0, 2, stream);
     if (rc == 0) rc = launch_set_f_pass(dev_inst(k), host_table[k], src, 0, 1, 2, stream);
     if (rc == 0) rc = launch_fill_u32((unsigned*)(ws + in.off_flags), 0u, 1, stream);
@@ -895,9 +892,9 @@ struct Engine {
     if (!rings_cover(1)) return fail(DUGKS_E_STATE, "Dirichlet data does not cover the current step");
     const int count = two_steps_ok() && rings_cover(2) ? 2 : 1;
     // keep the 16-bit slots: the trial steps accumulate into them
-    std::vector<std::vector<float>> saved(inst.size(), std::vector<float>(4));
+    std::vector<std::vector<float>> saved(inst.size(), std::vector<float>(kSlots));
     for (size_t k = 0; k < inst.size(); ++k) {
-      hipError_t e = hipMemcpyAsync(saved[k].data(), ws + inst[k].off_slots, 4 * sizeof(float),
+      hipError_t e = hipMemcpyAsync(saved[k].data(), ws + inst[k].off_slots, kSlots * sizeof(float),
                                     hipMemcpyDeviceToHost, stream);
       if (e != hipSuccess) return hipfail(e, "save slots");
     }
@@ -929,7 +926,7 @@ struct Engine {
     int rc = choose_launch(best.rows_per_wave, best.waves_per_block, best.schedule, best.xcd_remap);
     if (rc) return rc;
     for (size_t k = 0; k < inst.size(); ++k) {
-      e = hipMemcpyAsync(ws + inst[k].off_slots, saved[k].data(), 4 * sizeof(float),
+      e = hipMemcpyAsync(ws + inst[k].off_slots, saved[k].data(), kSlots * sizeof(float),
                          hipMemcpyHostToDevice, stream);
       if (e != hipSuccess) return hipfail(e, "restore slots");
       rc = launch_fill_u32((unsigned*)(ws + inst[k].off_flags), 0u, 1, stream);
@@ -1231,10 +1228,12 @@ int dugks_checkpoint(dugks_ctx* ctx, void* host_buf, size_t* len) {
   char* dst = (char*)host_buf + sizeof(hd);
   hipError_t e = hipMemcpyAsync(dst, ctx->ws + in.off_buf[ctx->cur], payload,
                                 hipMemcpyDeviceToHost, ctx->stream);
+  float slots[dugks::kSlots];
   if (e == hipSuccess)
-    e = hipMemcpyAsync(hd.slots, ctx->ws + in.off_slots, sizeof(hd.slots), hipMemcpyDeviceToHost, ctx->stream);
+    e = hipMemcpyAsync(slots, ctx->ws + in.off_slots, sizeof(slots), hipMemcpyDeviceToHost, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) return ctx->hipfail(e, "checkpoint copy");
+  for (int i = 0; i < 4; ++i) hd.slots[i] = *std::max_element(slots + i * dugks::kSlotWays, slots + (i + 1) * dugks::kSlotWays);
   hd.payload_checksum = dugks::fnv1a(dst, payload);
   memcpy(host_buf, &hd, sizeof(hd));
   *len = need;
@@ -1263,8 +1262,12 @@ int dugks_restore(dugks_ctx* ctx, const void* host_buf, size_t len) {
   if (hd.step < 0) return ctx->fail(DUGKS_E_FORMAT, "negative step");
   hipError_t e = hipMemcpyAsync(ctx->ws + in.off_buf[0], src, payload, hipMemcpyHostToDevice,
                                 ctx->stream);
+  // the next step's slot starts empty (a saved one may hold an older step's maximum)
+  float slots[dugks::kSlots] = {0};
+  for (int i = 0; i < 4; ++i)
+    if (i != (int)(hd.step & 3)) slots[i * dugks::kSlotWays] = hd.slots[i];
   if (e == hipSuccess)
-    e = hipMemcpyAsync(ctx->ws + in.off_slots, hd.slots, sizeof(hd.slots), hipMemcpyHostToDevice, ctx->stream);
+    e = hipMemcpyAsync(ctx->ws + in.off_slots, slots, sizeof(slots), hipMemcpyHostToDevice, ctx->stream);
   if (e == hipSuccess) {
     if (dugks::launch_fill_u32((unsigned*)(ctx->ws + in.off_flags), 0u, 1, ctx->stream)) e = hipErrorUnknown;
   }

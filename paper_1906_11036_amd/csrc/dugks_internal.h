@@ -21,6 +21,7 @@ constexpr int kMaxCoef = 8;     // E_i(phi) has degree <= 7 (C has degree 2*4-1)
 constexpr int kStripLanes = 64; // one wave covers 64 columns ...
 constexpr int kStripCols = 62;  // ... of which 62 are updated; lanes 0 and 63 are halo
 constexpr int kStripCols2 = 60; // columns updated by a wave that takes two steps (two halo lanes each side)
+constexpr int kSlotWays = 64;   // values of a slot (its maximum counts)
 constexpr int kGeo = 5;
 constexpr int kRhoCoef = 4;     // B'(phi) has degree <= 3
 constexpr int kMaxSrcTerms = DUGKS_MAX_SRC_TERMS;
@@ -53,7 +54,7 @@ struct alignas(64) InstDev {
   const float* colgeo_f;   // float copies
   const float* rowgeo_f;
   const double* ring;      // Dirichlet data, ring_steps x ring_len (or null)
-  float* slots;            // 16-bit storage: 4 max|f~ - E| slots (unscaled)
+  float* slots;            // 16-bit storage: 4 max|f~ - E| slots (unscaled) of kSlotWays values each
   unsigned* flags;         // DUGKS_FLAG_* bits, sticky
   long long plane;         // elements per plane = ny * pitch
   unsigned buf_bytes;      // bytes of one buffer (< 4 GiB, the buffer resource range)
@@ -119,8 +120,6 @@ int launch_step_fused(const StepArgs& a, const Launch& l, void* stream, int meas
 // goes to buffer parity ^ 1
 int launch_step2(const StepArgs& a, const Launch& l, void* stream);
 int launch_step_plain(const StepArgs& a, int nx, int ny, void* stream);
-// zero slots[(step + which) & 3] of every instance
-int launch_clear_slot(const InstDev* insts, int ninst, long long step, int which, void* stream);
 int launch_init_eq(const InstDev* d, const InstDev& h, const double* phi, int parity, void* stream);
 // pass 0: max |f~ - E| into slots[slot]; pass 1: encode f~ with that slot's scale
 int launch_set_f_pass(const InstDev* d, const InstDev& h, const double* f, int parity, int pass,

@@ -131,6 +131,18 @@ template <int ST> __host__ __device__ inline float neq_scale_for(float m) {
   else return neq_scale(m);
 }
 
+// The maxima behind the scales: slot i of an instance is the largest of its
+// kSlotWays values (one address took the atomics of every wave of the instance:
+// 1024^2 bf16neq 24.5 us a step at its best launch, 15.4 spread; 700 x 333 in
+// 2004 waves 30 and 14.6).
+__device__ __forceinline__ float slot_max(const InstDev* __restrict__ I, int slot) {   // whole waves only
+  float m = I->slots[slot * kSlotWays + (threadIdx.x & 63)];
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+  return m;
+}
+static_assert(kSlotWays == 64, "one value a lane");
+
 // ------------------------------------------------------------ DPP helpers
 // wave_shr:1 -> lane l receives lane l-1; wave_shl:1 -> lane l receives lane l+1.
 // Lanes without a source (0 for shr, 63 for shl) read 0 (bound_ctrl); their
@@ -717,8 +729,13 @@ __device__ __forceinline__ void step_item(const InstDev* __restrict__ I, const W
 
   Scales sc{1.0f, 1.0f};
   if constexpr (Stor<ST>::neq) {
-    sc.inv_in = 1.0f / neq_scale_for<ST>(I->slots[(step + 2) & 3]);
-    sc.out = neq_scale_for<ST>(I->slots[(step + 3) & 3]);
+    if constexpr (ST == DUGKS_F16NEQ) {   // (bfloat16 is stored unscaled)
+      sc.inv_in = 1.0f / neq_scale_for<ST>(slot_max(I, (int)((step + 2) & 3)));
+      sc.out = neq_scale_for<ST>(slot_max(I, (int)((step + 3) & 3)));
+    }
+    // slot (step + 1) & 3, neither read nor written by this step, is cleared for
+    // the next one by the instance's first item
+    if (it.x0 == 0 && it.y0 == 0) I->slots[((step + 1) & 3) * kSlotWays + lane] = 0.0f;
     eq.scale_g_16();
     eq.top_to_vgpr();
   }
@@ -992,13 +1009,12 @@ __device__ __forceinline__ void step_item(const InstDev* __restrict__ I, const W
     // wave maximum of |f~_i - E_i| (i >= 1) over updated cells -> the instance's slot
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    // Every wave of the instance aims at one address: a wave whose maximum does
-    // not exceed what it reads there leaves the atomic out (the value only
-    // grows, so a stale read costs an atomic and no more).
+    // The waves spread over the slot's values.  (Reading the value first, to
+    // leave atomics out, kept every wave waiting at its end: 0.03 ms a step of 64
+    // instances in bf16neq.)
     if (lane == 0 && mx > 0.0f) {
-      unsigned* slot = (unsigned*)(I->slots + (measure ? (int)((step + 3) & 3) : (int)(step & 3)));
-      if (__float_as_uint(mx) > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        atomicMax(slot, __float_as_uint(mx));
+      const int way = (it.x0 / kStripCols + 7 * it.y0) & (kSlotWays - 1);
+      atomicMax((unsigned*)(I->slots + (int)((step + (measure ? 3 : 0)) & 3) * kSlotWays + way), __float_as_uint(mx));
     }
   }
   if (__any(bad) && lane == 0) atomicOr(I->flags, (unsigned)DUGKS_FLAG_NONFINITE);
@@ -1292,15 +1308,6 @@ void k_step2(const InstDev* __restrict__ insts, const WorkItem* __restrict__ ite
   }
 }
 
-#ifndef DUGKS_PART
-// Clear slot (step+which)&3 of every instance before a 16-bit step.
-__global__ void k_clear_next_slot(const InstDev* __restrict__ insts, int ninst, long long step,
-                                  int which) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < ninst) insts[i].slots[(step + which) & 3] = 0.0f;
-}
-
-#endif
 // ------------------------------------------------------- plain FP64 step
 // One thread per cell; every neighbour value is read from global memory and
 // g of the 3x3 neighbourhood is recomputed per cell.
@@ -1486,12 +1493,13 @@ __global__ void k_set_f(const InstDev* __restrict__ I, const double* __restrict_
     }
   } else {
     float m = 0.0f;
-    if (in) encode_neq<Q, ST>(I, buf, off, v, pass == 1 ? neq_scale_for<ST>(I->slots[slot]) : 0.0f, &m);
+    const float s = pass == 1 ? neq_scale_for<ST>(slot_max(I, slot)) : 0.0f;
+    if (in) encode_neq<Q, ST>(I, buf, off, v, s, &m);
     if (pass == 0) {
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
       if ((threadIdx.x & 63) == 0 && m > 0.0f)
-        atomicMax((unsigned*)(I->slots + slot), __float_as_uint(m));
+        atomicMax((unsigned*)(I->slots + slot * kSlotWays + (blockIdx.y & (kSlotWays - 1))), __float_as_uint(m));
     }
   }
 }
@@ -1553,11 +1561,11 @@ template <int Q, int ST>
 __global__ void k_get_f(const InstDev* __restrict__ I, double* __restrict__ out, int parity,
                         long long step) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y;
+  float inv_s = 1.0f;
+  if constexpr (Stor<ST>::neq) inv_s = 1.0f / neq_scale_for<ST>(slot_max(I, (int)((step + 2) & 3)));
   if (i >= I->nx || j >= I->ny) return;
   const long long off = (long long)j * I->pitch + i;
   const long long N = (long long)I->nx * I->ny;
-  float inv_s = 1.0f;
-  if constexpr (Stor<ST>::neq) inv_s = 1.0f / neq_scale_for<ST>(I->slots[(step + 2) & 3]);
   double f[Q];
   decode<Q, ST>(I, (const char*)I->buf[parity], off, inv_s, f);
 #pragma unroll
@@ -1645,14 +1653,17 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ partia
 }
 
 // out[0..5] the sums, one wave each; out[6..8] the instance's flags and its
-// four scale slots as stored, so that one copy brings the whole diagnosis.
+// four scale slots, so that one copy brings the whole diagnosis.
 __global__ __launch_bounds__(64 * 6) void k_reduce_final(const InstDev* __restrict__ I,
                                                          const double* __restrict__ partial,
                                                          double* __restrict__ out) {
   const int v = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const double s = sum_partials(partial, v);
   if (lane == 0) out[v] = s;
-  if (v == 0 && lane < 4) ((float*)(out + 7))[lane] = I->slots[lane];
+  if (v < 4) {
+    const float m = slot_max(I, v);
+    if (lane == 0) ((float*)(out + 7))[v] = m;
+  }
   if (v == 1 && lane == 0) ((unsigned*)(out + 6))[0] = I->flags[0];
 }
 
@@ -1842,12 +1853,6 @@ int launch_step2(const StepArgs& a, const Launch& l, void* stream) {
     return a.q == 9 ? launch_step2_q_st<9, DUGKS_F64>(a, l, stream) : launch_step2_q_st<5, DUGKS_F64>(a, l, stream);
   if (a.storage != DUGKS_F32) return -1;
   return a.q == 9 ? launch_step2_q_st<9, DUGKS_F32>(a, l, stream) : launch_step2_q_st<5, DUGKS_F32>(a, l, stream);
-}
-
-int launch_clear_slot(const InstDev* insts, int ninst, long long step, int which, void* stream) {
-  hipLaunchKernelGGL(k_clear_next_slot, dim3((ninst + 255) / 256), dim3(256), 0, S(stream), insts,
-                     ninst, step, which);
-  DUGKS_CHECK_LAUNCH();
 }
 
 template <int Q>
