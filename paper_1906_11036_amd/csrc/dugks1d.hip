@@ -29,6 +29,7 @@
 #include <vector>
 
 #include "dugks1d.h"
+#include "host_copy.h"
 
 namespace dugks1 {
 
@@ -331,6 +332,7 @@ struct dugks1_ctx {
   // Dirichlet data
   const double* ghosts = nullptr;
   int ghosts_n = 0, ghosts_pos = 0;
+  dugks::HostCopy host_copy;
   bool have_gprev = false;     // a previous step's ghost pair exists (in the slot or the array)
 
   int fail(int rc, const std::string& m) { err = m; return rc; }
@@ -665,9 +667,8 @@ static int read_out(dugks1_ctx* x, double* out, int on_device, int what) {
   else
     hipLaunchKernelGGL(k_get1<float>, grid, block, 0, S1(x), (const float*)st, dst, x->nx, x->pitch, what);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess && !on_device)
-    e = hipMemcpyAsync(out, dst, sizeof(double) * count, hipMemcpyDeviceToHost, S1(x));
-  if (e == hipSuccess) e = hipStreamSynchronize(S1(x));
+  if (e == hipSuccess)
+    e = on_device ? hipStreamSynchronize(S1(x)) : x->host_copy.out(out, dst, sizeof(double) * count, S1(x));
   if (e != hipSuccess) return x->hipfail(e, "read out");
   return DUGKS_OK;
 }

@@ -16,6 +16,7 @@
 
 #include "dugks3d.h"
 #include "dugks3d_internal.h"
+#include "host_copy.h"
 
 using namespace dugks3;
 
@@ -88,6 +89,7 @@ struct dugks3_ctx {
          off_widths = 0, off_partial = 0, off_out = 0, off_stage = 0, total = 0;
   size_t buf_bytes = 0, stage_bytes = 0;
   Inst3 host{};
+  dugks::HostCopy host_copy;
   bool initialised = false;
   long long step = 0;
   const double* ring = nullptr;   // Dirichlet data (device, caller-owned)
@@ -261,9 +263,8 @@ struct dugks3_ctx {
     const int rc = want_f ? launch_get_f3(dev(), host, dst, (int)(step & 1), stream)
                           : launch_get_phi3(dev(), host, dst, (int)(step & 1), step, stream);
     if (rc) return fail(DUGKS_E_HIP, "read-out launch failed");
-    hipError_t er = on_device ? hipSuccess
-                              : hipMemcpyAsync(out, dst, count * sizeof(double), hipMemcpyDeviceToHost, stream);
-    if (er == hipSuccess) er = hipStreamSynchronize(stream);
+    const hipError_t er =
+        on_device ? hipStreamSynchronize(stream) : host_copy.out(out, dst, count * sizeof(double), stream);
     return er == hipSuccess ? DUGKS_OK : hipfail(er, "read-out");
   }
 };

@@ -15,6 +15,7 @@
 
 #include "dugks.h"
 #include "dugks_internal.h"
+#include "host_copy.h"
 
 namespace dugks {
 
@@ -273,6 +274,7 @@ struct Engine {
   bool use_graph = true;
   long long graph_steps = 0, eager_steps = 0;   // steps replayed / launched one by one
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  HostCopy host_copy;
 
   int ncoef_launch() const {
     int m = 2;
@@ -822,11 +824,7 @@ struct Engine {
     }
     int rc = launchf(dst);
     if (rc) { if (tmp) (void)hipFree(tmp); return fail(DUGKS_E_HIP, "read launch failed"); }
-    if (!on_device) {
-      e = hipMemcpyAsync(out, tmp, n, hipMemcpyDeviceToHost, stream);
-      if (e != hipSuccess) { (void)hipFree(tmp); return hipfail(e, "copy out"); }
-    }
-    e = hipStreamSynchronize(stream);
+    e = on_device ? hipStreamSynchronize(stream) : host_copy.out(out, tmp, n, stream);
     if (tmp) (void)hipFree(tmp);
     if (e != hipSuccess) return hipfail(e, "read");
     return DUGKS_OK;

@@ -1,0 +1,112 @@
+// Device-to-host copies into ordinary (pageable) memory.
+//
+// The runtime's own copy moves such memory through a pinned buffer with one
+// thread: about 10 GB/s.  Large copies go through two pinned chunks here, each
+// filled by the copy engine while a few threads empty the other: a pass that
+// reads 2^24 binary64 values back 22.9 -> 14.3 ms.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <string.h>
+
+#include <atomic>
+#include <thread>
+
+namespace dugks {
+
+// Owned by one context and used by one call at a time, as the context is; the
+// pinned memory is taken at the first large copy and freed with the context.
+class HostCopy {
+ public:
+  HostCopy() = default;
+  HostCopy(const HostCopy&) = delete;
+  HostCopy& operator=(const HostCopy&) = delete;
+  ~HostCopy() {
+    for (int b = 0; b < 2; ++b) {
+      if (pin_[b]) (void)hipHostFree(pin_[b]);
+      if (ev_[b]) (void)hipEventDestroy(ev_[b]);
+    }
+  }
+
+  // n bytes from device memory to dst, after the work enqueued on s; complete
+  // when it returns.
+  hipError_t out(void* dst, const void* src, size_t n, hipStream_t s) {
+    if (n < kLeast || !ready()) return plain(dst, src, n, s);
+    const size_t chunks = (n + kChunk - 1) / kChunk;
+    std::atomic<size_t> filled{0}, emptied{0};   // chunks filled; slices emptied
+    std::atomic<bool> stop{false};
+    auto slice = [&](size_t i, int w) {
+      const size_t at = i * kChunk, len = n - at < kChunk ? n - at : kChunk;
+      const size_t lo = len * w / kThreads, hi = len * (w + 1) / kThreads;
+      memcpy((char*)dst + at + lo, (const char*)pin_[i & 1] + lo, hi - lo);
+      emptied.fetch_add(1, std::memory_order_release);
+    };
+    auto work = [&](int w) {
+      for (size_t i = 0; i < chunks; ++i) {
+        while (filled.load(std::memory_order_acquire) <= i) {
+          if (stop.load(std::memory_order_relaxed)) return;
+          std::this_thread::yield();
+        }
+        slice(i, w);
+      }
+    };
+    std::thread team[kThreads - 1];
+    int started = 0;
+    try {
+      for (; started < kThreads - 1; ++started) team[started] = std::thread(work, started + 1);
+    } catch (...) {   // no threads to be had: the plain copy
+      stop = true;
+      for (int t = 0; t < started; ++t) team[t].join();
+      return plain(dst, src, n, s);
+    }
+    auto fill = [&](size_t i) {
+      const size_t at = i * kChunk, len = n - at < kChunk ? n - at : kChunk;
+      hipError_t e = hipMemcpyAsync(pin_[i & 1], (const char*)src + at, len, hipMemcpyDeviceToHost, s);
+      return e == hipSuccess ? hipEventRecord(ev_[i & 1], s) : e;
+    };
+    hipError_t e = fill(0);
+    if (e == hipSuccess && chunks > 1) e = fill(1);
+    for (size_t i = 0; i < chunks && e == hipSuccess; ++i) {
+      e = hipEventSynchronize(ev_[i & 1]);
+      if (e != hipSuccess) break;
+      filled.store(i + 1, std::memory_order_release);
+      slice(i, 0);
+      while (emptied.load(std::memory_order_acquire) < (i + 1) * kThreads) std::this_thread::yield();
+      if (i + 2 < chunks) e = fill(i + 2);
+    }
+    stop = true;
+    for (auto& t : team) t.join();
+    const hipError_t d = hipStreamSynchronize(s);   // nothing may still write the pinned chunks
+    return e == hipSuccess ? d : e;
+  }
+
+ private:
+  static constexpr size_t kChunk = size_t(4) << 20;
+  static constexpr size_t kLeast = size_t(16) << 20;   // below, the first use's pinning costs what the threads gain
+  static constexpr int kThreads = 4;
+  void* pin_[2] = {nullptr, nullptr};
+  hipEvent_t ev_[2] = {nullptr, nullptr};
+
+  static hipError_t plain(void* dst, const void* src, size_t n, hipStream_t s) {
+    const hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  }
+  bool ready() {
+    for (int b = 0; b < 2; ++b) {
+      if (!pin_[b] && hipHostMalloc(&pin_[b], kChunk, hipHostMallocDefault) != hipSuccess) {
+        pin_[b] = nullptr;
+        (void)hipGetLastError();
+        return false;
+      }
+      if (!ev_[b] && hipEventCreateWithFlags(&ev_[b], hipEventDisableTiming) != hipSuccess) {
+        ev_[b] = nullptr;
+        (void)hipGetLastError();
+        return false;
+      }
+    }
+    return true;
+  }
+};
+
+}  // namespace dugks

@@ -174,3 +174,19 @@ def test_four_steps_a_launch(n, bc, storage):
             e.step(1, auto_ghosts=False)
         assert np.array_equal(a.get_f(), e.get_f())
         assert np.array_equal(a.get_phi_prev(), e.get_phi_prev())
+
+
+def test_large_host_read_out():
+    """Host read-outs of many megabytes go through pinned chunks emptied by several
+    threads: every value arrives, at sizes that are no multiple of a chunk or of
+    the threads (and twice from one solver)."""
+    for n in ((1 << 21) + 5, (1 << 22) - 3):
+        p = W.random_problem1d(41, n, bc=P)
+        rng = np.random.default_rng(n)
+        f, prev = rng.standard_normal((3, n)), rng.standard_normal(n)
+        s = dg.Solver1D(p, "f64")
+        for _ in range(2):
+            s.set_state(f, prev)
+            assert np.array_equal(s.get_f(), f)
+            assert np.array_equal(s.get_phi_prev(), prev)
+            f, prev = f[:, ::-1].copy(), prev[::-1].copy()
