@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce1(const T* __restrict__ s
 
 // One wave a value: lanes add the nblocks (<= kRedBlocks) partial sums of their
 // share in block order (loads in flight together), then the lanes' tree.  One
-// thread walking them all took 372 us, this 4 us.
+// thread walking them all took 372 us, this 6.5 us.
 __global__ __launch_bounds__(64 * 6) void k_reduce1_final(const double* __restrict__ partial, int nblocks,
                                                           double* __restrict__ out) {
   const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
