@@ -189,3 +189,39 @@ def test_fused_source_autotune_keeps_state(storage):
     assert np.array_equal(s.get_f(), f0)
     s.step(3)
     assert np.array_equal(s.get_f(), ref.get_f())
+
+
+@pytest.mark.parametrize("bc", [(P, P, P), (M, D, P)])
+@pytest.mark.parametrize("q", [19, 15, 7])
+@pytest.mark.parametrize("nterms", [1, 2, 3])
+def test_source_term_counts(nterms, q, bc):
+    """Up to two terms and more than two, with and without walls, are kernels of
+    their own: binary64 against the oracle to 1e-12, binary32 within 2 n eps32
+    (relative L2 of phi), both in the default launch and with two rows a tile
+    and three planes a chunk (bitwise the same)."""
+    p = W.random_problem3d(1000 + q, 65, 5, 7, q=q, bc=bc, stretched=True, bdeg=2, ddeg=1)
+    p.src_terms = W.random_source_terms3d(1010 + nterms, p, nterms=nterms, amp=0.8)
+    n = 4
+    rings = p.rings(n)
+    say(f"case 3d source terms {nterms} q={q} bc={bc}")
+    o = Oracle3D(p, openmp=True)
+    o.step(n, rings)
+    for storage in ("f64", "f32"):
+        f = []
+        for ln in (None, (2, 3)):
+            s = dg.Solver3D(p, storage=storage)
+            if ln is not None:
+                s.set_launch(*ln)
+            s.set_phi(p.phi0)
+            if rings is not None:
+                s.set_dirichlet(rings)
+            s.step(n)
+            f.append(s.get_f())
+            phi = s.get_phi()
+            s.close()
+        assert np.array_equal(f[0], f[1])
+        if storage == "f64":
+            assert rel_max(f[0], o.get_f()) <= 1e-12
+        else:
+            ref = o.get_phi()
+            assert np.sqrt(((phi - ref) ** 2).sum() / (ref ** 2).sum()) <= 2 * n * EPS32
