@@ -309,3 +309,25 @@ def test_full_size_one_step_sampled_3d(storage, tol):
     err = float(np.abs(got - ref).max() / np.abs(ref).max())
     say(f"  sampled max rel err {err:.2e} over {len(cells)} cells")
     assert err <= tol
+
+
+@pytest.mark.parametrize("bc", [(P, P, P), (D, M, P), (M, P, D)])
+@pytest.mark.parametrize("nx,ny,nz", [(24, 24, 24), (5, 3, 1), (63, 9, 21), (64, 5, 40)])
+def test_default_launch(nx, ny, nz, bc):
+    """The default launch splits nz into equal chunks, down to one plane each on
+    the smallest meshes: the same bits as one chunk over all planes."""
+    for q in (19, 15, 7):
+        for storage in ("f64", "f32"):
+            p = W.random_problem3d(1200 + q + nx, nx, ny, nz, q=q, bc=bc, stretched=True, bdeg=2)
+            say(f"case 3d default launch {nx}x{ny}x{nz} q={q} {storage} bc={bc}")
+            out = []
+            for planes in (None, nz):
+                s = solver(p, storage)
+                if planes is not None:
+                    s.set_launch(s.info()["rows_per_block"], planes)
+                s.set_phi(p.phi0)
+                if D in bc:
+                    s.set_dirichlet(p.rings(3))
+                s.step(3)
+                out.append(s.get_f())
+            assert np.array_equal(out[0], out[1])
