@@ -158,8 +158,8 @@ int dugks3_reduce(dugks3_ctx* ctx, const double* ref_dev, double* mass, double* 
  * is refused.  With a source the step takes the split-direction kernel's
  * instantiation with mirror code for every mesh and lattice (D3Q7 then with
  * two waves a row).  Defaults, with a source or without: 2 rows (binary64),
- * 4 rows (binary32; D3Q15 with walls: 2); planes: D3Q15 and D3Q19 the power
- * of two in 4..128 that
+ * 4 rows (binary32; D3Q15 with walls: 2); planes: D3Q15 and D3Q19 the even
+ * split of nz into chunks of at most 128 that
  * minimises (rounds of blocks over 256 CUs) x (planes + 3), D3Q7 32 halved
  * down to 4 while the grid would have fewer than 512 blocks.  Every launch
  * gives bitwise the same result.
@@ -203,7 +203,8 @@ size_t dugks3_batch_workspace_bytes(const dugks3_batch* b);
  * bound.  Errors: E_ARG, E_NOMEM, E_STATE, E_HIP. */
 int dugks3_batch_bind(dugks3_batch* b, void* dev_workspace, size_t bytes, void* hip_stream);
 /* Rows and planes per block for the batch's launch (ranges as
- * dugks3_set_launch; defaults 2 rows binary64, 4 binary32, 32 planes). */
+ * dugks3_set_launch; defaults 2 rows binary64, 4 binary32, planes by the
+ * instances' sizes). */
 int dugks3_batch_set_launch(dugks3_batch* b, int rows_per_block, int planes_per_block);
 /* nsteps steps of every instance, one launch each; the instances must be at
  * the same step count, with Dirichlet data covering the steps (E_STATE) and
