@@ -133,7 +133,7 @@ typedef struct dugks_info {
   long long work_items;
   size_t state_bytes;     /* bytes of one f~ buffer (read once and written once per step) */
   long long graph_steps;  /* steps replayed from captured hipGraphs since dugks_bind */
-  long long eager_steps;  /* steps launched one by one since dugks_bind */
+  long long eager_steps;  /* steps launched outside graphs since dugks_bind */
   int xy_symmetric;       /* 1: E_i and E_j have bitwise the same coefficients for every pair
                              i, j whose velocities differ by swapping x and y (B_x = B_y,
                              D_xx = D_yy), in every instance of the context or batch; the

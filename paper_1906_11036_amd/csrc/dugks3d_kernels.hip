@@ -2,14 +2,15 @@
 // (eq. 2.28), D3Q19 (eq. 2.6) and D3Q7 (Remark 3).
 //
 // Fused step: a block owns a strip of 62 columns (64 lanes: one halo column
-// each side), a tile of rows (one or two waves per row) and a chunk of planes, which
+// each side), a tile of rows (one to four waves per row) and a chunk of planes, which
 // it sweeps in z, with g of three planes of its rows and the two halo rows in
 // LDS.  Per plane and cell it computes the west face (x; the east face is the
 // next lane's west face), both y faces and the top face (z; the bottom face is
 // the previous plane's top face) and the update.  x neighbours come from
 // whole-wave DPP shifts, as in the 2-D kernels.  D3Q15 and D3Q19 (both
-// storages) stage raw f~ through LDS with direct buffer-to-LDS loads and give
-// each row two waves, one per half of the directions (k_step3p).  D3Q7, whose
+// storages) give each row two or four waves, each a part of the directions
+// (k_step3p): with two, raw f~ is staged through LDS with direct buffer-to-LDS
+// loads; with four, loaded into registers two planes ahead.  D3Q7, whose
 // registers are no constraint, gives each row one wave: binary32 staged the
 // same way (k_step3s), binary64 with its window in registers and one wave on
 // each halo row (k_step3h).
