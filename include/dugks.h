@@ -242,7 +242,9 @@ int dugks_set_f(dugks_ctx* ctx, const double* f, int on_device);
  * the library's own, launched on the bound stream after a one-thread kernel
  * that writes the run's first step index to the workspace, from which the
  * captured kernels take the time of their Dirichlet data and sources); the
- * rest, and every step of the plain kernel, are launched one by one.
+ * rest, and every step of the plain kernel, are launched one by one.  Binary64
+ * and binary32 storage without a source takes two steps a launch (the same
+ * bits), except where a Dirichlet axis stands beside a periodic one.
  * dugks_info counts both kinds.  Errors: E_STATE (not initialised, Dirichlet
  * data exhausted), E_HIP. */
 int dugks_step(dugks_ctx* ctx, int nsteps);
