@@ -278,16 +278,14 @@ namespace {
 // Planes a chunk when the caller has not chosen.  D3Q15 and D3Q19: the blocks
 // of a step run in rounds of 256 CUs x blocks a CU (from their LDS: 160 KiB a CU)
 // and a block takes about (planes + 3) plane times (its prologue loads and makes
-// two planes): of the lengths that split the tallest mesh evenly, at most 128,
-// the one that minimises rounds x (planes + 3), the longer on a tie.  Against the
-// powers of two alone, and 32 planes for every batch (us a step): D3Q19 96^3
-// binary32 69 -> 51, binary64 121 -> 106, 200^3 binary32 472 -> 435, 32^3 binary64
-// 16.1 -> 12.4, 100 x 120 x 77 binary64 127 -> 109; batches of 3, 8, 16 meshes of
-// 24^3..80^3, D3Q19 binary32 77 -> 44, 143 -> 97, 235 -> 197; 64 of 48^3..80^3
-// 1297 -> 1179.  D3Q7, whose smaller blocks share a CU: 32 planes, halved down to 4
-// while the grid has fewer than 512 blocks (the rule above, 64^3 binary32: 14.8
-// us against 10.9).
-int default_planes(const std::vector<const dugks3_ctx*>& inst, int rows, size_t lds) {
+// two planes): the length that minimises rounds x (planes + 3), the longer on a
+// tie, of the powers of two in 4..128 for one mesh, and for a batch (`split`) of
+// the lengths up to 128 that split its tallest mesh evenly.  Against 32 planes for
+// every batch (us a step, D3Q19 binary32): batches of 3, 8, 16 meshes of
+// 24^3..80^3 77 -> 44, 143 -> 97, 235 -> 197; 64 of 48^3..80^3 1297 -> 1179.  D3Q7,
+// whose smaller blocks share a CU: 32 planes, halved down to 4 while the grid
+// has fewer than 512 blocks.
+int default_planes(const std::vector<const dugks3_ctx*>& inst, int rows, size_t lds, bool split) {
   int nz = 1;
   for (auto* x : inst) nz = std::max(nz, x->n[2]);
   const long long slots = 256 * std::max<long long>(1, (long long)(163840 / std::max<size_t>(lds, 1)));
@@ -304,14 +302,14 @@ int default_planes(const std::vector<const dugks3_ctx*>& inst, int rows, size_t 
   }
   int best = 1;
   long long best_cost = -1;
-  for (int chunks = (nz + 127) / 128, last = 0; chunks <= nz; ++chunks) {
-    const int planes = (nz + chunks - 1) / chunks;
-    if (planes == last) continue;
-    last = planes;
-    const long long blocks = grid(planes);
-    const long long cost = ((blocks + slots - 1) / slots) * (planes + 3);
+  auto take = [&](int planes) {
+    const long long cost = ((grid(planes) + slots - 1) / slots) * (planes + 3);
     if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = planes; }
-  }
+  };
+  if (split)
+    for (int chunks = (nz + 127) / 128; chunks <= nz; ++chunks) take((nz + chunks - 1) / chunks);
+  else
+    for (int planes = 128; planes >= 4; planes /= 2) take(planes);
   return best;
 }
 }  // namespace
@@ -393,7 +391,7 @@ int dugks3_create(dugks3_ctx** out, int nx, int ny, int nz, const double* xf, co
   // walls: two, which lets two blocks share a CU) -- the fastest at 256^3
   const bool walls = p->bc[0] != DUGKS_BC_PERIODIC || p->bc[1] != DUGKS_BC_PERIODIC || p->bc[2] != DUGKS_BC_PERIODIC;
   x->launch.rows = p->storage == DUGKS_F64 ? 2 : ((q == 15 && walls) ? 2 : 4);
-  x->launch.planes = default_planes({x}, x->launch.rows, x->lds_bytes(x->launch));
+  x->launch.planes = default_planes({x}, x->launch.rows, x->lds_bytes(x->launch), false);
   return DUGKS_OK;
 }
 
@@ -755,7 +753,7 @@ int dugks3_batch_create(dugks3_batch** out, int n, dugks3_ctx* const* ctxs) {
     b->inst.push_back(c);
   }
   b->launch.rows = b->storage == DUGKS_F64 ? 2 : 4;
-  b->launch.planes = default_planes({b->inst.begin(), b->inst.end()}, b->launch.rows, b->lds_bytes(b->launch));
+  b->launch.planes = default_planes({b->inst.begin(), b->inst.end()}, b->launch.rows, b->lds_bytes(b->launch), true);
   b->layout();
   return b->upload();
 }

@@ -314,8 +314,7 @@ def test_full_size_one_step_sampled_3d(storage, tol):
 @pytest.mark.parametrize("bc", [(P, P, P), (D, M, P), (M, P, D)])
 @pytest.mark.parametrize("nx,ny,nz", [(24, 24, 24), (5, 3, 1), (63, 9, 21), (64, 5, 40)])
 def test_default_launch(nx, ny, nz, bc):
-    """The default launch splits nz into equal chunks, down to one plane each on
-    the smallest meshes: the same bits as one chunk over all planes."""
+    """The default launch gives the same bits as one chunk over all planes."""
     for q in (19, 15, 7):
         for storage in ("f64", "f32"):
             p = W.random_problem3d(1200 + q + nx, nx, ny, nz, q=q, bc=bc, stretched=True, bdeg=2)
