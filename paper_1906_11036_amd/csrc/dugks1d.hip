@@ -475,6 +475,9 @@ int dugks1_create(dugks1_ctx** out, int nx, const double* xf, const dugks1_param
     x->face64[(size_t)m * 3 + 1] = wl / dn;                // c_i = 0
     x->face64[(size_t)m * 3 + 2] = (wl - h * p->c) / dn;   // c_i = +c
   }
+  if (p->bc == DUGKS_BC_PERIODIC)   // face nx is face 0: the same factors to the last bit, so that
+    for (int k = 0; k < 3; ++k)     // a wrapped cell in a launch of several steps sees the same fluxes
+      x->face64[(size_t)nx * 3 + k] = x->face64[k];
   x->upd64.assign(nx, 0.0);
   for (int j = 0; j < nx; ++j) x->upd64[j] = dt * p->c / x->wd[j + 1];
   // a mesh whose widths agree to 1e-12 is stepped as uniform (geometry from the index)

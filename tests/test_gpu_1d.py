@@ -176,6 +176,30 @@ def test_four_steps_a_launch(n, bc, storage):
         assert np.array_equal(a.get_phi_prev(), e.get_phi_prev())
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 55, 56, 57, 64, 113, 400, 900])
+@pytest.mark.parametrize("bc", [P, D])
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_four_steps_a_launch_on_stretched_meshes(n, bc, storage):
+    """The same on stretched meshes, whose geometry comes from tables: past a
+    periodic seam a lane steps the cell that it wraps to with the factors of
+    that cell's own faces."""
+    p = W.random_problem1d(970 + n, n, bc=bc, stretched=True)
+    say(f"case 1d four steps, stretched, n={n} bc={bc} {storage}")
+    a, e = dg.Solver1D(p, storage), dg.Solver1D(p, storage)
+    for s in (a, e):
+        s.set_phi(p.phi0)
+    for steps in (8, 9, 40):
+        if bc == D:
+            g = a.ghost_table(steps)
+            for s in (a, e):
+                s.set_dirichlet(g)
+        a.step(steps, auto_ghosts=False)
+        for _ in range(steps):
+            e.step(1, auto_ghosts=False)
+        assert np.array_equal(a.get_f(), e.get_f())
+        assert np.array_equal(a.get_phi_prev(), e.get_phi_prev())
+
+
 def test_large_host_read_out():
     """Host read-outs of many megabytes go through pinned chunks emptied by several
     threads: every value arrives, at sizes that are no multiple of a chunk or of
