@@ -244,7 +244,11 @@ int dugks_set_f(dugks_ctx* ctx, const double* f, int on_device);
  * captured kernels take the time of their Dirichlet data and sources); the
  * rest, and every step of the plain kernel, are launched one by one.  Binary64
  * and binary32 storage without a source takes two steps a launch (the same
- * bits), except where a Dirichlet axis stands beside a periodic one.
+ * bits), except where a Dirichlet axis stands beside a periodic one.  While the
+ * caller captures the bound stream every step is launched by itself, so that
+ * the caller's graph of an even number of steps ends in the buffer it began in
+ * and can be replayed (binary64 and binary32 storage, steps that do not depend
+ * on the time).
  * dugks_info counts both kinds.  Errors: E_STATE (not initialised, Dirichlet
  * data exhausted), E_HIP. */
 int dugks_step(dugks_ctx* ctx, int nsteps);

@@ -94,7 +94,9 @@ int dugks1_set_state(dugks1_ctx* ctx, const double* f, const double* phi_prev, i
  * (periodic walls). */
 int dugks1_set_dirichlet(dugks1_ctx* ctx, const double* ghosts, int nsteps);
 
-/* Advance nsteps >= 0 steps (asynchronous).  Errors: E_STATE (not bound, no
+/* Advance nsteps >= 0 steps (asynchronous), four a launch (the same bits), or
+ * one a launch while the caller captures the bound stream, whose graph of an
+ * even number of steps can then be replayed.  Errors: E_STATE (not bound, no
  * state, Dirichlet data exhausted: nothing is stepped), E_HIP. */
 int dugks1_step(dugks1_ctx* ctx, int nsteps);
 

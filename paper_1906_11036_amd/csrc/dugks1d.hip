@@ -642,8 +642,13 @@ int dugks1_step(dugks1_ctx* x, int nsteps) {
   if (nsteps < 0) return x->fail(DUGKS_E_ARG, "nsteps must be >= 0");
   if (x->p.bc == DUGKS_BC_DIRICHLET && x->ghosts_n - x->ghosts_pos < nsteps)
     return x->fail(DUGKS_E_STATE, "Dirichlet data exhausted: supply more with dugks1_set_dirichlet");
+  // A caller's capture takes one step a launch: an even number of them ends in
+  // the buffer that it began in, so that the graph can be replayed.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(S1(x), &cap) != hipSuccess) (void)hipGetLastError();
+  const bool multi = cap != hipStreamCaptureStatusActive;
   for (int left = nsteps; left > 0;) {
-    const int n = left >= kMultiSteps ? kMultiSteps : 1;
+    const int n = multi && left >= kMultiSteps ? kMultiSteps : 1;
     if (x->p.storage == DUGKS_F64) n == 1 ? launch_steps<double, 1>(x) : launch_steps<double, kMultiSteps>(x);
     else n == 1 ? launch_steps<float, 1>(x) : launch_steps<float, kMultiSteps>(x);
     hipError_t e = hipGetLastError();

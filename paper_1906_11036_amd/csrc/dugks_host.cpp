@@ -711,6 +711,19 @@ struct Engine {
     return DUGKS_OK;
   }
 
+  // Whether the caller is capturing the bound stream.  Steps are then launched
+  // one by one, none from the library's graphs (which a capture does not record):
+  // an even number of them ends in the buffer that it began in, so that the
+  // caller's graph advances the state at every replay.
+  bool caller_captures() const {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    return st == hipStreamCaptureStatusActive;
+  }
+
   int do_steps(int nsteps) {
     if (nsteps < 0) return fail(DUGKS_E_ARG, "nsteps < 0");
     if (!bound()) return fail(DUGKS_E_STATE, "not bound");
@@ -719,7 +732,9 @@ struct Engine {
     int remaining = nsteps;
     // captured launches read their step index (the time of Dirichlet data and
     // sources) as an offset from a base written before each replay
-    const bool graphable = use_graph && !plain;
+    const bool captured = caller_captures();
+    const bool graphable = use_graph && !plain && !captured;
+    const bool pairs = two_steps_ok() && !captured;
     while (remaining > 0) {
       if (need_measure) {
         int rc = enqueue_step(step, cur, 1, stream, true);
@@ -741,7 +756,7 @@ struct Engine {
         graph_steps += kGraphSteps[w];
       } else {
         // pairs start at even steps, so that a run reaches the graphs' phase
-        const int count = remaining >= 2 && (step & 1) == 0 && two_steps_ok() ? 2 : 1;
+        const int count = remaining >= 2 && (step & 1) == 0 && pairs ? 2 : 1;
         int rc = enqueue_step(step, cur, count, stream, false);
         if (rc) return rc;
         cur ^= 1;

@@ -200,6 +200,32 @@ def test_four_steps_a_launch_on_stretched_meshes(n, bc, storage):
         assert np.array_equal(a.get_phi_prev(), e.get_phi_prev())
 
 
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_captured_steps_can_be_replayed(storage):
+    """An even number of steps captured by the caller ends in the buffer it began
+    in, so each replay advances the state (b and d constant in time)."""
+    import torch
+    p = W.random_problem1d(960, 200, bc=P)
+    p.coef = (0.0, 0.0, 0.3, 0.0, 0.0, 0.8, 0.0)
+    say(f"case 1d captured steps {storage}")
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        for n in (2, 4, 6):
+            a, e = dg.Solver1D(p, storage), dg.Solver1D(p, storage)
+            for s in (a, e):
+                s.set_phi(p.phi0)
+                s.step(4)
+            st.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=st):
+                a.step(n)
+            for _ in range(4):
+                g.replay()
+                e.step(n)
+                st.synchronize()
+                assert np.array_equal(a.get_f(), e.get_f()), n
+
+
 def test_large_host_read_out():
     """Host read-outs of many megabytes go through pinned chunks emptied by several
     threads: every value arrives, at sizes that are no multiple of a chunk or of

@@ -80,3 +80,31 @@ def test_state_after_an_odd_number_of_launches():
             for _ in range(5):
                 c.step(1)
             assert np.array_equal(b.get_f(), c.get_f())
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("bc", [W.PERIODIC, W.MIRROR])
+def test_captured_steps_can_be_replayed(storage, bc):
+    """An even number of steps captured by the caller ends in the buffer it began
+    in, so each replay advances the state (eager work and reads between the
+    replays)."""
+    import torch
+    p = W.random_problem(78, 130, 41, bcx=bc, bcy=bc, bdeg=1, ddeg=1)
+    if bc == W.MIRROR:
+        p.bx, p.by = (0.0, 0.1), (0.0, 0.1)
+    print(f"case captured steps {storage} bc={bc}", flush=True)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        for n in (2, 4, 6):
+            a, e = (solver(p, storage, 3, 1, None) for _ in range(2))
+            for s in (a, e):
+                s.step(2)
+            st.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=st):
+                a.step(n)
+            for _ in range(4):
+                g.replay()
+                e.step(n)
+                st.synchronize()
+                assert np.array_equal(a.get_f(), e.get_f()), n
