@@ -340,9 +340,9 @@ struct Engine {
     size_t off = 0;
     off_table = off; off += align256(sizeof(InstDev) * inst.size());
     build_items();
-    off_items = off; off += align256(sizeof(WorkItem) * std::max<size_t>(items.size(), 1) * 1);
-    // room for a work list with the smallest rows-per-wave the tuner may pick
-    off += align256(sizeof(WorkItem) * max_items_bound());
+    // the longest work lists (one row an item), so that the size depends on the
+    // meshes and the storage alone and not on the launch or the sources
+    off_items = off; off += align256(sizeof(WorkItem) * max_items_bound());
     off_items2 = off;
     if (two_storage()) off += align256(sizeof(WorkItem) * max_items_bound(kStripCols2));
     off_partial = off; off += align256(sizeof(double) * 8 * reduce_partials());
@@ -783,7 +783,7 @@ struct Engine {
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
       persistent_blocks = cus * (16 / wpb);
       build_items();
-      if (items.size() > max_items_bound() + 1) return fail(DUGKS_E_ARG, "work list too long");
+      if (items.size() > max_items_bound()) return fail(DUGKS_E_ARG, "work list too long");
       hipError_t e = upload_items();
       if (e != hipSuccess) return hipfail(e, "upload work list");
       e = hipStreamSynchronize(stream);

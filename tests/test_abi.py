@@ -88,6 +88,27 @@ def test_create_and_workspace_size():
         lib.dugks_destroy(h)
 
 
+@pytest.mark.parametrize("storage", [L.F64, L.F32])
+@pytest.mark.parametrize("bc", [L.BC_PERIODIC, L.BC_MIRROR])
+def test_workspace_size_does_not_depend_on_launch_or_sources(storage, bc):
+    """The size a caller asked for after dugks_create still holds after a source or
+    a launch is set (either may change the number of work items)."""
+    lib = L.lib()
+    for nx, ny in ((1024, 1024), (61, 45), (1, 1)):
+        rc, h = _create(nx=nx, ny=ny, storage=storage, bc=(bc,) * 4)
+        assert rc == 0
+        n = lib.dugks_workspace_bytes(h)
+        g = C.c_void_p(1 << 20)   # a device address, not followed before binding
+        assert lib.dugks_set_source(h, g, 0.0) == 0
+        assert lib.dugks_workspace_bytes(h) == n
+        assert lib.dugks_set_source(h, None, 0.0) == 0
+        assert lib.dugks_workspace_bytes(h) == n
+        for rows in (1, 2, 7, 64, 4096):
+            assert lib.dugks_set_launch(h, rows, 1, 0, 1) == 0
+            assert lib.dugks_workspace_bytes(h) == n
+        lib.dugks_destroy(h)
+
+
 def test_calls_before_bind_report_state_errors():
     lib = L.lib()
     rc, h = _create()
