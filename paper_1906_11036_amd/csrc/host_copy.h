@@ -51,24 +51,29 @@ class HostCopy {
         slice(i, w);
       }
     };
-    std::thread team[kThreads - 1];
-    int started = 0;
-    try {
-      for (; started < kThreads - 1; ++started) team[started] = std::thread(work, started + 1);
-    } catch (...) {   // no threads to be had: the plain copy
-      stop = true;
-      for (int t = 0; t < started; ++t) team[t].join();
-      return plain(dst, src, n, s);
-    }
     auto fill = [&](size_t i) {
       const size_t at = i * kChunk, len = n - at < kChunk ? n - at : kChunk;
       hipError_t e = hipMemcpyAsync(pin_[i & 1], (const char*)src + at, len, hipMemcpyDeviceToHost, s);
       return e == hipSuccess ? hipEventRecord(ev_[i & 1], s) : e;
     };
+    // The first chunk comes after all the work enqueued on s, which may be long:
+    // the threads start when it is there, so that nothing spins until then.
     hipError_t e = fill(0);
     if (e == hipSuccess && chunks > 1) e = fill(1);
+    if (e == hipSuccess) e = hipEventSynchronize(ev_[0]);
+    std::thread team[kThreads - 1];
+    int started = 0;
+    if (e == hipSuccess) {
+      try {
+        for (; started < kThreads - 1; ++started) team[started] = std::thread(work, started + 1);
+      } catch (...) {   // no threads to be had: the plain copy
+        stop = true;
+        for (int t = 0; t < started; ++t) team[t].join();
+        return plain(dst, src, n, s);
+      }
+    }
     for (size_t i = 0; i < chunks && e == hipSuccess; ++i) {
-      e = hipEventSynchronize(ev_[i & 1]);
+      if (i > 0) e = hipEventSynchronize(ev_[i & 1]);
       if (e != hipSuccess) break;
       filled.store(i + 1, std::memory_order_release);
       slice(i, 0);
@@ -76,7 +81,7 @@ class HostCopy {
       if (i + 2 < chunks) e = fill(i + 2);
     }
     stop = true;
-    for (auto& t : team) t.join();
+    for (int t = 0; t < started; ++t) team[t].join();
     const hipError_t d = hipStreamSynchronize(s);   // nothing may still write the pinned chunks
     return e == hipSuccess ? d : e;
   }
