@@ -32,7 +32,7 @@ class HostCopy {
   // n bytes from device memory to dst, after the work enqueued on s; complete
   // when it returns.
   hipError_t out(void* dst, const void* src, size_t n, hipStream_t s) {
-    if (n < kLeast || !ready()) return plain(dst, src, n, s);
+    if (n < kLeast || !ready(s)) return plain(dst, src, n, s);
     const size_t chunks = (n + kChunk - 1) / kChunk;
     std::atomic<size_t> filled{0}, emptied{0};   // chunks filled; slices emptied
     std::atomic<bool> stop{false};
@@ -92,25 +92,38 @@ class HostCopy {
   static constexpr int kThreads = 4;
   void* pin_[2] = {nullptr, nullptr};
   hipEvent_t ev_[2] = {nullptr, nullptr};
+  int ev_device_[2] = {0, 0};
 
   static hipError_t plain(void* dst, const void* src, size_t n, hipStream_t s) {
     const hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, s);
     return e == hipSuccess ? hipStreamSynchronize(s) : e;
   }
-  bool ready() {
-    for (int b = 0; b < 2; ++b) {
+  // The pinned chunks and the events, which belong to the device of the stream
+  // that they are recorded on (the caller's current device may be another).
+  bool ready(hipStream_t s) {
+    int now = 0;
+    hipDevice_t dev = 0;
+    bool ok = hipGetDevice(&now) == hipSuccess && hipStreamGetDevice(s, &dev) == hipSuccess;
+    const bool move = ok && dev != now;
+    if (move) ok = hipSetDevice(dev) == hipSuccess;
+    for (int b = 0; b < 2 && ok; ++b) {
       if (!pin_[b] && hipHostMalloc(&pin_[b], kChunk, hipHostMallocDefault) != hipSuccess) {
         pin_[b] = nullptr;
-        (void)hipGetLastError();
-        return false;
+        ok = false;
       }
-      if (!ev_[b] && hipEventCreateWithFlags(&ev_[b], hipEventDisableTiming) != hipSuccess) {
+      if (ev_[b] && ev_device_[b] != dev) {
+        (void)hipEventDestroy(ev_[b]);
         ev_[b] = nullptr;
-        (void)hipGetLastError();
-        return false;
+      }
+      if (ok && !ev_[b]) {
+        ok = hipEventCreateWithFlags(&ev_[b], hipEventDisableTiming) == hipSuccess;
+        if (!ok) ev_[b] = nullptr;
+        ev_device_[b] = dev;
       }
     }
-    return true;
+    if (move) (void)hipSetDevice(now);
+    if (!ok) (void)hipGetLastError();
+    return ok;
   }
 };
 

@@ -14,13 +14,21 @@
 
 static int waits = 0;             // event waits so far
 static useconds_t first_wait = 0; // length of the first one
+static int current = 0;           // the current device
+struct Event { int device; };
+static int device_of(hipStream_t s) { return s ? *(int*)s : current; }   // a stream is its device's number
 
 extern "C" {
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return (*p = malloc(n)) ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t) new Event{current}; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { delete (Event*)e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {   // an event belongs to the device it was created on
+  return ((Event*)e)->device == device_of(s) ? hipSuccess : hipErrorInvalidHandle;
+}
+hipError_t hipGetDevice(int* d) { *d = current; return hipSuccess; }
+hipError_t hipSetDevice(int d) { current = d; return hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) { *d = device_of(s); return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) {
   if (waits++ == 0 && first_wait) usleep(first_wait);
   return hipSuccess;
@@ -79,9 +87,26 @@ static int idle() {
   return dst == src && waited < copy + 0.4 ? 0 : 1;   // one thread waiting actively would add 0.8
 }
 
+// a stream of another device than the current one, then of the current one
+static int devices() {
+  dugks::HostCopy hc;
+  const size_t n = size_t(17) << 20;
+  const std::vector<unsigned char> src = pattern(n);
+  int dev[3] = {1, 0, 2};
+  for (int& d : dev) {
+    std::vector<unsigned char> dst(n, 0);
+    if (hc.out(dst.data(), src.data(), n, (hipStream_t)&d) != hipSuccess || dst != src || current != 0) {
+      fprintf(stderr, "device %d\n", d);
+      return 1;
+    }
+  }
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "values")) return values();
   if (!strcmp(what, "idle")) return idle();
+  if (!strcmp(what, "devices")) return devices();
   return 2;
 }
