@@ -32,7 +32,7 @@ class HostCopy {
   // n bytes from device memory to dst, after the work enqueued on s; complete
   // when it returns.
   hipError_t out(void* dst, const void* src, size_t n, hipStream_t s) {
-    if (n < kLeast || !ready(s)) return plain(dst, src, n, s);
+    if (n < kLeast || !pageable(dst) || !ready(s)) return plain(dst, src, n, s);
     const size_t chunks = (n + kChunk - 1) / kChunk;
     std::atomic<size_t> filled{0}, emptied{0};   // chunks filled; slices emptied
     std::atomic<bool> stop{false};
@@ -97,6 +97,13 @@ class HostCopy {
   static hipError_t plain(void* dst, const void* src, size_t n, hipStream_t s) {
     const hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, s);
     return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  }
+  // Memory that the runtime knows (pinned, managed) is written by the copy engine itself.
+  static bool pageable(const void* p) {
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type == hipMemoryTypeUnregistered;
+    (void)hipGetLastError();   // (an address that is not the runtime's may also be an error)
+    return true;
   }
   // The pinned chunks and the events, which belong to the device of the stream
   // that they are recorded on (the caller's current device may be another).

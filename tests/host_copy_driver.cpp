@@ -15,6 +15,8 @@
 static int waits = 0;             // event waits so far
 static useconds_t first_wait = 0; // length of the first one
 static int current = 0;           // the current device
+static const void* pinned = nullptr;   // an address that the runtime knows
+static int to_pinned = 0;         // copies enqueued to it
 struct Event { int device; };
 static int device_of(hipStream_t s) { return s ? *(int*)s : current; }   // a stream is its device's number
 
@@ -34,7 +36,13 @@ hipError_t hipEventSynchronize(hipEvent_t) {
   return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  if (d == pinned) ++to_pinned;
   memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+  memset(a, 0, sizeof(*a));
+  a->type = p == pinned ? hipMemoryTypeHost : hipMemoryTypeUnregistered;
   return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
@@ -103,10 +111,21 @@ static int devices() {
   return 0;
 }
 
+// memory that is pinned already is filled by one copy
+static int direct() {
+  dugks::HostCopy hc;
+  const size_t n = size_t(24) << 20;
+  const std::vector<unsigned char> src = pattern(n);
+  std::vector<unsigned char> dst(n, 0);
+  pinned = dst.data();
+  return hc.out(dst.data(), src.data(), n, nullptr) == hipSuccess && dst == src && to_pinned == 1 ? 0 : 1;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "values")) return values();
   if (!strcmp(what, "idle")) return idle();
   if (!strcmp(what, "devices")) return devices();
+  if (!strcmp(what, "direct")) return direct();
   return 2;
 }

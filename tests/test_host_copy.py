@@ -24,7 +24,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["values", "idle", "devices"])
+@pytest.mark.parametrize("case", ["values", "idle", "devices", "direct"])
 def test_host_copy(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
