@@ -236,19 +236,19 @@ int dugks_set_phi(dugks_ctx* ctx, const double* phi, int on_device);
  * format) and reset step and time to 0. */
 int dugks_set_f(dugks_ctx* ctx, const double* f, int on_device);
 
-/* Advance nsteps >= 0 steps, asynchronously on the bound stream.  Runs of
- * four or more steps that start at a step divisible by 4 are replayed from
- * captured hipGraphs of 32 and 4 steps (captured on first use on a stream of
- * the library's own, launched on the bound stream after a one-thread kernel
- * that writes the run's first step index to the workspace, from which the
- * captured kernels take the time of their Dirichlet data and sources); the
- * rest, and every step of the plain kernel, are launched one by one.  Binary64
- * and binary32 storage without a source takes two steps a launch (the same
- * bits), except where a Dirichlet axis stands beside a periodic one.  While the
- * caller captures the bound stream every step is launched by itself, so that
- * the caller's graph of an even number of steps ends in the buffer it began in
- * and can be replayed (binary64 and binary32 storage, steps that do not depend
- * on the time).
+/* Advance nsteps >= 0 steps, asynchronously on the bound stream.  A run that
+ * holds four or more steps from a step divisible by 4 replays captured
+ * hipGraphs of 32 and 4 steps from there (captured on first use on a stream of
+ * the library's own, launched on the bound stream after a small kernel that
+ * writes the first step's index, from which the captured kernels take the time
+ * of their Dirichlet data and sources, and the instances' buffers to the
+ * workspace); the rest, and every step of the plain kernel, are launched from
+ * the host.  Binary64 and binary32 storage without a source takes two steps a
+ * launch wherever two are left (the same bits), except where a Dirichlet axis
+ * stands beside a periodic one.  While the caller captures the bound stream
+ * every step is launched by itself, so that the caller's graph of an even
+ * number of steps ends in the buffer it began in and can be replayed (binary64
+ * and binary32 storage, steps that do not depend on the time).
  * dugks_info counts both kinds.  Errors: E_STATE (not initialised, Dirichlet
  * data exhausted), E_HIP. */
 int dugks_step(dugks_ctx* ctx, int nsteps);

@@ -22,8 +22,8 @@ namespace dugks {
 static constexpr uint32_t kMagicCtx = 0x44554731u;    // "DUG1"
 static constexpr uint32_t kMagicBatch = 0x44554742u;  // "DUGB"
 // Steps per captured graph: a long graph for long runs and a short one so that
-// any run of four or more steps from a phase-0 step replays a graph.  Both are
-// multiples of 4, the period of the buffer parity and the 16-bit scale slots.
+// any run of four or more steps from a phase-0 step (one divisible by 4) replays
+// a graph.  Both take an even number of launches.
 static constexpr int kGraphSteps[2] = {32, 4};
 
 static constexpr int kSlots = 4 * kSlotWays;
@@ -267,10 +267,9 @@ struct Engine {
   long long step = 0;
   int cur = 0;   // the buffer that holds the state
   bool need_measure = false;
-  // graphs (kGraphSteps[0] and kGraphSteps[1] steps from a phase-0 step), for
-  // either buffer holding the state
-  hipGraphExec_t graph_exec[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
-  hipGraph_t graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+  // graphs of kGraphSteps[0] and kGraphSteps[1] steps
+  hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
+  hipGraph_t graph[2] = {nullptr, nullptr};
   bool use_graph = true;
   long long graph_steps = 0, eager_steps = 0;   // steps replayed / launched one by one
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -338,7 +337,7 @@ struct Engine {
 
   void layout() {
     size_t off = 0;
-    off_table = off; off += align256(sizeof(InstDev) * inst.size());
+    off_table = off; off += align256(sizeof(InstDev) * 2 * inst.size());   // and the replays'
     build_items();
     // the longest work lists (one row an item), so that the size depends on the
     // meshes and the storage alone and not on the launch or the sources
@@ -536,8 +535,10 @@ struct Engine {
 
   int upload_tables() {
     fill_table();
-    hipError_t e = hipMemcpyAsync(ws + off_table, host_table.data(), sizeof(InstDev) * inst.size(),
-                                  hipMemcpyHostToDevice, stream);
+    hipError_t e = hipSuccess;
+    for (int t = 0; t < 2 && e == hipSuccess; ++t)
+      e = hipMemcpyAsync((InstDev*)(ws + off_table) + t * inst.size(), host_table.data(), sizeof(InstDev) * inst.size(),
+                         hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return hipfail(e, "upload instance table");
     e = upload_items();
     if (e != hipSuccess) return hipfail(e, "upload work list");
@@ -603,6 +604,9 @@ struct Engine {
   }
 
   const InstDev* dev_table() const { return (const InstDev*)(ws + off_table); }
+  // what captured launches read: the instances with the buffer that holds the
+  // state first (written before each replay)
+  InstDev* replay_table() const { return (InstDev*)(ws + off_table) + inst.size(); }
   const InstDev* dev_inst(int k) const { return dev_table() + k; }
 
   // step n with the state in buffer `buf`
@@ -664,10 +668,13 @@ struct Engine {
 
   // Enqueue step n (count == 2: steps n and n + 1 in one launch) on stream s,
   // from buffer buf into the other (captured: index n after the base written
-  // before each replay).
+  // before each replay, buffers of the replay table).
   int enqueue_step(long long n, int buf, int count, hipStream_t s, bool measure, bool captured = false) {
     StepArgs a = step_args(n, buf);
-    if (captured) a.step_base = (const long long*)(ws + off_stepbase);
+    if (captured) {
+      a.insts = replay_table();
+      a.step_base = (const long long*)(ws + off_stepbase);
+    }
     int rc;
     if (plain) {
       rc = launch_step_plain(a, inst[0].nx, inst[0].ny, s);
@@ -683,30 +690,29 @@ struct Engine {
   }
 
   void drop_graph() {
-    for (int w = 0; w < 2; ++w)
-      for (int b = 0; b < 2; ++b) {
-        if (graph_exec[w][b]) { (void)hipGraphExecDestroy(graph_exec[w][b]); graph_exec[w][b] = nullptr; }
-        if (graph[w][b]) { (void)hipGraphDestroy(graph[w][b]); graph[w][b] = nullptr; }
-      }
+    for (int w = 0; w < 2; ++w) {
+      if (graph_exec[w]) { (void)hipGraphExecDestroy(graph_exec[w]); graph_exec[w] = nullptr; }
+      if (graph[w]) { (void)hipGraphDestroy(graph[w]); graph[w] = nullptr; }
+    }
   }
 
-  // Capture kGraphSteps[w] steps starting at step index 0 from buffer b;
-  // replayed at any step divisible by 4 (same 16-bit slot phase).  The number of
-  // launches is even, so the state is in buffer b again after a replay.
-  int build_graph(int w, int b) {
+  // Capture kGraphSteps[w] steps as steps 0, 1, ... from the replay table's first
+  // buffer; a replay adds its first step's index.  The number of launches is
+  // even, so the state is in the same buffer after it.
+  int build_graph(int w) {
     hipError_t e = hipStreamBeginCapture(cap_stream, hipStreamCaptureModeRelaxed);
     if (e != hipSuccess) return hipfail(e, "begin capture");
     int rc = DUGKS_OK;
     const int count = two_steps_ok() ? 2 : 1;
-    int buf = b;
+    int buf = 0;
     for (int k = 0; k < kGraphSteps[w] && rc == DUGKS_OK; k += count, buf ^= 1)
       rc = enqueue_step(k, buf, count, cap_stream, false, true);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(cap_stream, &g);
     if (rc) { if (g) (void)hipGraphDestroy(g); return rc; }
     if (e != hipSuccess) return hipfail(e, "end capture");
-    graph[w][b] = g;
-    e = hipGraphInstantiate(&graph_exec[w][b], graph[w][b], nullptr, nullptr, 0);
+    graph[w] = g;
+    e = hipGraphInstantiate(&graph_exec[w], graph[w], nullptr, nullptr, 0);
     if (e != hipSuccess) { drop_graph(); return hipfail(e, "instantiate graph"); }
     return DUGKS_OK;
   }
@@ -731,7 +737,8 @@ struct Engine {
     if (!rings_cover(nsteps)) return fail(DUGKS_E_STATE, "Dirichlet data does not cover the requested steps");
     int remaining = nsteps;
     // captured launches read their step index (the time of Dirichlet data and
-    // sources) as an offset from a base written before each replay
+    // sources) as an offset from a base, and their buffers from a table, written
+    // before each replay
     const bool captured = caller_captures();
     const bool graphable = use_graph && !plain && !captured;
     const bool pairs = two_steps_ok() && !captured;
@@ -741,22 +748,25 @@ struct Engine {
         if (rc) return rc;
         need_measure = false;
       }
-      const int w = remaining >= kGraphSteps[0] ? 0 : 1;
-      if (graphable && remaining >= kGraphSteps[1] && (step & 3) == 0) {
-        if (!graph_exec[w][cur]) {
-          int rc = build_graph(w, cur);
+      // steps to the graphs' phase, and whether the run goes on to a graph there
+      const int lead = (int)((4 - (step & 3)) & 3);
+      const bool graphs = graphable && remaining >= lead + kGraphSteps[1];
+      if (graphs && lead == 0) {
+        const int w = remaining >= kGraphSteps[0] ? 0 : 1;
+        if (!graph_exec[w]) {
+          int rc = build_graph(w);
           if (rc) return rc;
         }
-        if (launch_set_i64((long long*)(ws + off_stepbase), step, stream))
+        if (launch_set_base(dev_table(), replay_table(), (int)inst.size(), cur,
+                            (long long*)(ws + off_stepbase), step, stream))
           return fail(DUGKS_E_HIP, "step base launch failed");
-        hipError_t e = hipGraphLaunch(graph_exec[w][cur], stream);
+        hipError_t e = hipGraphLaunch(graph_exec[w], stream);
         if (e != hipSuccess) return hipfail(e, "graph launch");
         step += kGraphSteps[w];
         remaining -= kGraphSteps[w];
         graph_steps += kGraphSteps[w];
       } else {
-        // pairs start at even steps, so that a run reaches the graphs' phase
-        const int count = remaining >= 2 && (step & 1) == 0 && pairs ? 2 : 1;
+        const int count = pairs && (graphs ? lead : remaining) >= 2 ? 2 : 1;
         int rc = enqueue_step(step, cur, count, stream, false);
         if (rc) return rc;
         cur ^= 1;

@@ -145,7 +145,11 @@ int reduce_partials();
 int launch_norms_noalloc(const InstDev* d, const InstDev& h, const double* ref, int parity,
                          long long step, const double* widths, double* out_dev, void* stream);
 int launch_fill_u32(unsigned* p, unsigned v, long long n, void* stream);
-int launch_set_i64(long long* p, long long v, void* stream);
+// Before a replay: base[0] = step (StepArgs::step_base), and the buffers of the n
+// instances of `replay` (read by the captured launches as from buffer 0) those of
+// `insts`, buffer `buf` first, so that one graph serves a state in either buffer.
+int launch_set_base(const InstDev* insts, InstDev* replay, int n, int buf, long long* base, long long step,
+                    void* stream);
 
 // Power-of-two scale of the 16-bit formats for a maximum |f~ - E| of m.
 float neq_scale_host(int storage, float m);

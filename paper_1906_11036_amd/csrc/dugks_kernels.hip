@@ -1711,8 +1711,14 @@ static int scratch_ptr(double** out) {
   return 0;
 }
 
-__global__ void k_set_i64(long long* p, long long v) {
-  if (threadIdx.x == 0) *p = v;
+__global__ void k_set_base(const InstDev* __restrict__ insts, InstDev* __restrict__ replay, int n, int buf,
+                           long long* __restrict__ base, long long step) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) *base = step;
+  if (i < n) {
+    replay[i].buf[0] = insts[i].buf[buf];
+    replay[i].buf[1] = insts[i].buf[buf ^ 1];
+  }
 }
 
 __global__ void k_fill_u32(unsigned* p, unsigned v, long long n) {
@@ -1959,8 +1965,9 @@ int launch_norms_noalloc(const InstDev* d, const InstDev& h, const double* ref, 
   DUGKS_CHECK_LAUNCH();
 }
 
-int launch_set_i64(long long* p, long long v, void* stream) {
-  hipLaunchKernelGGL(k_set_i64, dim3(1), dim3(64), 0, S(stream), p, v);
+int launch_set_base(const InstDev* insts, InstDev* replay, int n, int buf, long long* base, long long step,
+                    void* stream) {
+  hipLaunchKernelGGL(k_set_base, dim3((n + 63) / 64), dim3(64), 0, S(stream), insts, replay, n, buf, base, step);
   DUGKS_CHECK_LAUNCH();
 }
 

@@ -108,3 +108,27 @@ def test_captured_steps_can_be_replayed(storage, bc):
                 e.step(n)
                 st.synchronize()
                 assert np.array_equal(a.get_f(), e.get_f()), n
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16neq"])
+def test_runs_from_every_phase_and_either_buffer(storage):
+    """Runs that start at any step, with the state in either buffer (two steps a
+    launch, or a state restored at an odd step): one captured graph serves both."""
+    p = W.random_problem(79, 130, 41, bdeg=2, ddeg=2)
+    print(f"case runs from every phase {storage}", flush=True)
+    a, e = (solver(p, storage, 3, 1, None) for _ in range(2))
+    for n in (1, 6, 2, 11, 5, 40, 3, 9):
+        a.step(n)
+        for _ in range(n):
+            e.step(1)
+        assert np.array_equal(a.get_f(), e.get_f()), n
+    a.step(1)
+    blob = a.checkpoint()
+    b, c = (solver(p, storage, 2, 1, None) for _ in range(2))
+    for s in (b, c):
+        s.restore(blob)
+    b.step(41)
+    for _ in range(41):
+        c.step(1)
+    assert b.info()["graph_steps"] >= 36
+    assert np.array_equal(b.get_f(), c.get_f())
