@@ -300,7 +300,8 @@ int dugks_checkpoint(dugks_ctx* ctx, void* host_buf, size_t* len);
  * hash or checksum), E_STATE (not bound). */
 int dugks_restore(dugks_ctx* ctx, const void* host_buf, size_t len);
 
-/* Launch configuration: rows_per_wave (rows each wave marches, 1..4096),
+/* Launch configuration: rows_per_wave (rows each wave marches, 1..4096; the
+ * launches of two steps of dugks_step take half of it beside walls),
  * waves_per_block (1, 2 or 4; also 8 for binary32 and 16-bit storage without
  * a source, whose step kernel runs two waves per SIMD; setting a source later
  * turns an 8 into 4), schedule (DUGKS_SCHED_*), xcd_remap (0/1: map
@@ -310,7 +311,8 @@ int dugks_set_launch(dugks_ctx* ctx, int rows_per_wave, int waves_per_block, int
                      int xcd_remap);
 
 /* Time trial_steps steps for each candidate launch configuration and keep the
- * fastest.  Writes only the inactive buffer: the state is unchanged.  Every
+ * fastest, of launches of one step and, where dugks_step takes them, of two
+ * (dugks_info reports the latter's).  Writes only the inactive buffer: the state is unchanged.  Every
  * trial step reads the Dirichlet data of the current step.  Synchronises.
  * Errors: E_STATE (no state, or Dirichlet data not covering the current
  * step), E_HIP. */

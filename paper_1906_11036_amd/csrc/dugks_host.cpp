@@ -259,9 +259,10 @@ struct Engine {
   size_t total_bytes = 0;
   std::vector<InstDev> host_table;
   std::vector<WorkItem> items, items2;   // of the one-step and the two-step launches
-  Launch launch;
+  Launch launch;   // of the launches of two steps, where runs take them, else of all
+  Launch single;   // of the launches of one step
   bool launch_chosen = false;   // by the caller or the autotuner
-  int persistent_blocks = 0;
+  int cus = 256;
   // clock: every instance whose ready flag is set holds its state at `step`
   std::vector<char> ready;
   long long step = 0;
@@ -318,13 +319,10 @@ struct Engine {
       in.src_gam[j] = j < n ? gam[j] : 0.0;
     }
     drop_graph();
-    const Launch before = launch;
     if (!launch_chosen) default_launch();
-    if (launch.waves_per_block > 4 && !wide_blocks_ok()) launch.waves_per_block = 4;   // the source path runs 4-wave blocks
-    if (launch.rows_per_wave != before.rows_per_wave || launch.waves_per_block != before.waves_per_block) {
-      const int rc = set_launch(launch.rows_per_wave, launch.waves_per_block, launch.schedule, launch.xcd_remap);
-      if (rc) return rc;
-    }
+    if (!wide_blocks_ok())   // the source path runs 4-wave blocks
+      for (Launch* l : {&launch, &single}) l->waves_per_block = std::min(l->waves_per_block, 4);
+    build_items();
     return bound() ? upload_tables() : DUGKS_OK;
   }
   // 8-wave blocks need the step kernels compiled for two waves per SIMD
@@ -381,12 +379,16 @@ struct Engine {
   }
   // Row chunks of a strip.  A wave beside a wall takes the ghost-rule
   // instantiation, two to three times a row's work, so where every wave of a step
-  // is resident at once these set its time: strips beside an x wall march
-  // half the rows a wave, and so do the first and last chunk beside y walls.
+  // is resident at once these set its time: with half_edges strips beside an x wall
+  // march half the rows a wave, and so do the first and last chunk beside y walls
   // (512^2 Burgers binary32 11.9 -> 9.4 us a step, 1024^2 with mirror walls
-  // binary64 42.3 -> 31.1.)
-  template <class F> static void row_chunks(const Instance& in, int H, bool x_edge, F f) {
-    const int half = (H + 1) / 2;
+  // binary64 42.3 -> 31.1).  Launches of two steps always do so (4096^2 with mirror
+  // walls, binary32 179 -> 156, binary64 371 -> 335), those of one step by
+  // default or where the autotuner finds it faster; a caller's rows are taken as
+  // given.
+  template <class F> static void row_chunks(const Instance& in, const Launch& l, bool x_edge, F f) {
+    int H = l.rows_per_wave;
+    const int half = l.half_edges ? (H + 1) / 2 : H;
     if (x_edge && in.bcx != DUGKS_BC_PERIODIC) H = half;
     int y = 0, end = in.ny;
     if (in.bcy != DUGKS_BC_PERIODIC && H > half && in.ny > 2 * half) {
@@ -397,60 +399,90 @@ struct Engine {
     }
     for (; y < end; y += H) f(y, std::min(y + H, end));
   }
-  static double count_items(const Instance& in, int H, int cols) {
+  static double count_items(const Instance& in, const Launch& l, int cols) {
     const int strips = (in.nx + cols - 1) / cols, edges = std::min(strips, 2);
     double inner = 0, edge = 0;
-    row_chunks(in, H, false, [&](int, int) { inner += 1; });
-    row_chunks(in, H, true, [&](int, int) { edge += 1; });
+    row_chunks(in, l, false, [&](int, int) { inner += 1; });
+    row_chunks(in, l, true, [&](int, int) { edge += 1; });
     return (strips - edges) * inner + edges * edge;
   }
-  // Rows a wave marches when the caller has not chosen: a SIMD runs k = waves /
-  // 1024 of them, each H rows and a prologue worth c rows, and more than one at
-  // a time only fills the gaps of a row's latency: cost max(1, v k) (H + c).
-  // Binary32 and the 16-bit formats reach v = 0.75 with two or more waves a
-  // SIMD, binary64 and the sources hold one (v = 1).  Measured, two steps a
-  // launch, us a step over H: 512^2 binary32 8.6 (1), 6.1 (3), 6.2 (6), 11.0
-  // (16); 1024^2 15.2 (4), 14.3 (12), 16.3 (24), 36.6 (64); 4096^2 174 (8), 151
-  // (48), 165 (64); binary64 512^2 12.8 (2), 9.1 (6), 13.6 (12); 128^2 3.7 (1),
-  // 27.3 (32).
-  int default_rows() const {
+  double count_items(const Launch& l, int cols) const {
+    double n = 0;
+    for (auto& in : inst) n += count_items(in, l, cols);
+    return n;
+  }
+  bool any_wall() const {
+    for (auto& in : inst)
+      if (in.bcx != DUGKS_BC_PERIODIC || in.bcy != DUGKS_BC_PERIODIC) return true;
+    return false;
+  }
+  // The launch of one or two steps when the caller has not chosen.  Rows a wave
+  // marches: a SIMD runs k = waves / 1024 of them, each H rows and a prologue
+  // worth c rows, and more than one at a time only fills the gaps of a row's
+  // latency: cost max(1, v k) (H + c).  Binary32 and the 16-bit formats reach
+  // v = 0.75 with two or more waves a SIMD, binary64 holds one (v = 1); a single
+  // step of binary32 holds two, so an odd one out takes a whole turn (2048^2 with a
+  // source: 102 us a step at 24 rows, 90 at 12).  Measured, two steps a launch, us a step over H: 512^2 binary32 8.6 (1), 6.1 (3), 6.2
+  // (6), 11.0 (16); 1024^2 15.2 (4), 14.3 (12), 16.3 (24), 36.6 (64); 4096^2 174
+  // (8), 151 (48), 165 (64); binary64 512^2 12.8 (2), 9.1 (6), 13.6 (12); 128^2
+  // 3.7 (1), 27.3 (32).
+  // Beside walls a launch of one step may also leave the rows whole, for which the
+  // waves there end a little later: 0.15 (H + c) more.  us a step, whole and
+  // halved: 1024^2 binary64 33.5 and 31.2 (20 rows), 2048^2 binary32 80 and 90
+  // (24), 1400^2 binary64 67 and 85 (32), 4096^2 binary64 552 and 590 (32).
+  // Blocks of 4 waves (binary64: 2) once they fill the chip several times over,
+  // single waves before (they spread over more CUs).
+  Launch default_of(bool two) const {
     const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48};
-    const bool two = two_steps_ok();
-    const double v = (storage == DUGKS_F64 || any_source()) ? 1.0 : 0.75, c = two ? 3.5 : 2.5;
+    const double v = storage == DUGKS_F64 ? 1.0 : 0.75, c = two ? 3.5 : 2.5;
     const int cols = two ? kStripCols2 : kStripCols;
     double best_cost = 0;
-    int best = 0;
-    for (int H : cand) {
-      double waves = 0;
-      for (auto& in : inst) waves += count_items(in, H, cols);
-      const double k = waves / 1024.0;
-      const double cost = std::max(1.0, v * (k < 8 ? std::ceil(k) : k)) * (H + c);
-      if (best == 0 || cost <= best_cost) { best_cost = cost; best = H; }
+    Launch best;
+    for (int H : cand)
+      for (int half = two || !any_wall() ? 1 : 0; half < 2; ++half) {
+        Launch l;
+        l.rows_per_wave = H;
+        l.half_edges = half;
+        const double k = count_items(l, cols) / 1024.0;
+        double load = v * (k < 8 ? std::ceil(k) : k);
+        if (!two && storage == DUGKS_F32 && k < 8 && (int)std::ceil(k) % 2 == 1) load += 0.25;
+        const double cost = (std::max(1.0, load) + (half ? 0.0 : 0.15)) * (H + c);
+        if (best_cost == 0 || cost <= best_cost) { best_cost = cost; best = l; }
+      }
+    const double waves = count_items(best, kStripCols);
+    best.waves_per_block = waves < 4096 ? 1 : (storage == DUGKS_F64 ? 2 : 4);
+    // A single step of binary32 or binary64 streams its state: where it fills the
+    // chip many times over, shorter items keep the rows that two waves share in
+    // the L2.  us a step over rows x waves a block, without a source: 4096^2
+    // binary32 319 (32 x 4), 312 (16 x 2), 296 (12 x 4), 283 (12 x 8), binary64
+    // 534 (32 x 2), 511 (12 x 2); 256 instances of 64^2..1024^2 binary32 975 (48 x
+    // 4), 861 (12 x 4), 811 (12 x 8).  With one phi-free source term: binary32 344
+    // (32 x 4), 319 (20 x 4), binary64 575 (32 x 2), 563 (20 x 2).  More terms are
+    // bound by their arithmetic (three terms, binary64: 890 at 32 rows, 902 at 20).
+    if (!two && !neq() && waves >= 2 * 4096 && source_kind() < 2) {
+      best.rows_per_wave = std::min(best.rows_per_wave, any_source() ? 20 : 12);
+      if (wide_blocks_ok()) best.waves_per_block = 8;
     }
     return best;
   }
-  // The default launch: blocks of 4 waves (binary64: 2) once they fill the chip
-  // several times over, single waves before (they spread over more CUs).
+  // Where runs take two steps a launch, the steps left over and runs of one step
+  // have a launch of their own.
   void default_launch() {
-    launch = Launch{};
-    launch.rows_per_wave = default_rows();
-    double waves = 0;
-    for (auto& in : inst) waves += count_items(in, launch.rows_per_wave, kStripCols);
-    launch.waves_per_block = waves < 4096 ? 1 : (storage == DUGKS_F64 ? 2 : 4);
+    single = default_of(false);
+    launch = two_steps_ok() ? default_of(true) : single;
   }
-  void build_items_of(std::vector<WorkItem>& out, int cols) const {
+  void build_items_of(std::vector<WorkItem>& out, const Launch& l, int cols) const {
     out.clear();
     for (int k = 0; k < (int)inst.size(); ++k) {
       const Instance& in = inst[k];
-      const int H = launch.rows_per_wave;
       auto add = [&](bool x_edge) {   // row chunks, each over the strips that take them
-        row_chunks(in, H, x_edge, [&](int y0, int y1) {
+        row_chunks(in, l, x_edge, [&](int y0, int y1) {
           for (int x0 = 0; x0 < in.nx; x0 += cols)
             if (x_edge == (x0 == 0 || x0 + cols >= in.nx)) out.push_back(WorkItem{k, x0, y0, y1});
         });
       };
-      if (in.bcx == DUGKS_BC_PERIODIC) {
-        row_chunks(in, H, false, [&](int y0, int y1) {
+      if (in.bcx == DUGKS_BC_PERIODIC || !l.half_edges) {
+        row_chunks(in, l, false, [&](int y0, int y1) {
           for (int x0 = 0; x0 < in.nx; x0 += cols) out.push_back(WorkItem{k, x0, y0, y1});
         });
       } else {
@@ -460,8 +492,10 @@ struct Engine {
     }
   }
   void build_items() {
-    build_items_of(items, kStripCols);
-    if (two_storage()) build_items_of(items2, kStripCols2);
+    build_items_of(items, single, kStripCols);
+    Launch two = launch;
+    two.half_edges = 1;
+    if (two_storage()) build_items_of(items2, two, kStripCols2);
   }
   hipError_t upload_items() {
     hipError_t e = hipMemcpyAsync(ws + off_items, items.data(), sizeof(WorkItem) * items.size(),
@@ -577,12 +611,10 @@ struct Engine {
       if (e == hipSuccess) e = hipEventCreate(&ev1);
       if (e != hipSuccess) return hipfail(e, "create events");
     }
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
-      persistent_blocks = cus * (16 / launch.waves_per_block);
-    else
-      persistent_blocks = 256 * 4;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+      cus = 256;
     ready.assign(inst.size(), 0);
     step = 0;
     cur = 0;
@@ -620,7 +652,7 @@ struct Engine {
     a.q = inst[0].q;
     a.storage = storage;
     a.ncoef = ncoef_launch();
-    a.persistent_blocks = persistent_blocks;
+    a.persistent_blocks = cus * (16 / single.waves_per_block);
     a.src = source_kind();
     a.sym = 1;
     for (auto& in : inst) a.sym &= in.xy_sym ? 1 : 0;
@@ -681,9 +713,10 @@ struct Engine {
     } else if (count == 2) {
       a.items = (const WorkItem*)(ws + off_items2);
       a.nitems = (int)items2.size();
+      a.persistent_blocks = cus * (16 / launch.waves_per_block);
       rc = launch_step2(a, launch, s);
     } else {
-      rc = launch_step_fused(a, launch, s, measure ? 1 : 0);
+      rc = launch_step_fused(a, single, s, measure ? 1 : 0);
     }
     if (rc) return fail(DUGKS_E_HIP, std::string("step launch failed: ") + hipGetErrorString(hipGetLastError()));
     return DUGKS_OK;
@@ -778,20 +811,10 @@ struct Engine {
     return DUGKS_OK;
   }
 
-  int set_launch(int rows, int wpb, int sched, int xcd) {
-    if (rows < 1 || rows > 4096) return fail(DUGKS_E_ARG, "rows_per_wave out of range");
-    if (wpb != 1 && wpb != 2 && wpb != 4 && !(wpb == 8 && wide_blocks_ok()))
-      return fail(DUGKS_E_ARG, "waves_per_block must be 1, 2 or 4 (8: binary32 or 16-bit storage without a source)");
-    if (sched != DUGKS_SCHED_GRID && sched != DUGKS_SCHED_PERSISTENT) return fail(DUGKS_E_ARG, "bad schedule");
-    launch.rows_per_wave = rows;
-    launch.waves_per_block = wpb;
-    launch.schedule = sched;
-    launch.xcd_remap = xcd ? 1 : 0;
+  int use_launch(const Launch& l, const Launch& one) {
+    launch = l;
+    single = one;
     if (bound()) {
-      int dev = 0, cus = 256;
-      if (hipGetDevice(&dev) == hipSuccess)
-        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-      persistent_blocks = cus * (16 / wpb);
       build_items();
       if (items.size() > max_items_bound()) return fail(DUGKS_E_ARG, "work list too long");
       hipError_t e = upload_items();
@@ -803,10 +826,19 @@ struct Engine {
     return DUGKS_OK;
   }
 
+  // the caller's choice, for every launch
   int choose_launch(int rows, int wpb, int sched, int xcd) {
-    const int rc = set_launch(rows, wpb, sched, xcd);
-    if (rc == DUGKS_OK) launch_chosen = true;
-    return rc;
+    if (rows < 1 || rows > 4096) return fail(DUGKS_E_ARG, "rows_per_wave out of range");
+    if (wpb != 1 && wpb != 2 && wpb != 4 && !(wpb == 8 && wide_blocks_ok()))
+      return fail(DUGKS_E_ARG, "waves_per_block must be 1, 2 or 4 (8: binary32 or 16-bit storage without a source)");
+    if (sched != DUGKS_SCHED_GRID && sched != DUGKS_SCHED_PERSISTENT) return fail(DUGKS_E_ARG, "bad schedule");
+    Launch l;
+    l.rows_per_wave = rows;
+    l.waves_per_block = wpb;
+    l.schedule = sched;
+    l.xcd_remap = xcd ? 1 : 0;
+    launch_chosen = true;
+    return use_launch(l, l);
   }
 
   int set_phi(int k, const double* phi, int on_device) {
@@ -939,7 +971,7 @@ struct Engine {
   }
 
   // Time candidate launch configurations on the inactive buffer only (the
-  // buffers are not swapped, so the state is kept), two steps a launch where
+  // buffers are not swapped, so the state is kept): of one step, and of two where
   // runs of steps take them so.
   int autotune(int trials) {
     if (!bound()) return fail(DUGKS_E_STATE, "not bound");
@@ -958,31 +990,44 @@ struct Engine {
     }
     hipError_t e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return hipfail(e, "synchronise");
-    const Launch keep = launch;
-    Launch best = keep;
-    float best_ms = 1e30f;
     const int rows_c[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 128};   // short items: more waves on small grids
     const int wpb_c[] = {1, 2, 4, 8};
-    for (int sched = 0; sched < 2; ++sched)
-      for (int rows : rows_c)
-        for (int wpb : wpb_c) {
-          if (wpb == 8 && !wide_blocks_ok()) continue;
-          if (set_launch(rows, wpb, sched, 1)) return DUGKS_E_ARG;
-          // warm-up
-          for (int t = 0; t < 2; ++t)
-            if (enqueue_step(step, cur, count, stream, false)) return DUGKS_E_HIP;
-          e = hipEventRecord(ev0, stream);
-          for (int t = 0; t < trials && e == hipSuccess; ++t)
-            if (enqueue_step(step, cur, count, stream, false)) return DUGKS_E_HIP;
-          if (e == hipSuccess) e = hipEventRecord(ev1, stream);
-          if (e == hipSuccess) e = hipEventSynchronize(ev1);
-          float ms = 0;
-          if (e == hipSuccess) e = hipEventElapsedTime(&ms, ev0, ev1);
-          if (e != hipSuccess) return hipfail(e, "autotune timing");
-          if (ms < best_ms) { best_ms = ms; best = launch; }
-        }
-    int rc = choose_launch(best.rows_per_wave, best.waves_per_block, best.schedule, best.xcd_remap);
+    // the fastest launch of n steps; beside walls those of one step also with the rows halved
+    auto fastest = [&](int n, Launch& best) -> int {
+      float best_ms = 1e30f;
+      const int halves = n == 1 && any_wall() ? 2 : 1;
+      for (int cand = 0; cand < 2 * halves; ++cand)
+        for (int rows : rows_c)
+          for (int wpb : wpb_c) {
+            if (wpb == 8 && !wide_blocks_ok()) continue;
+            Launch l;
+            l.rows_per_wave = rows;
+            l.waves_per_block = wpb;
+            l.schedule = cand & 1;
+            l.half_edges = cand >> 1;
+            int rc = use_launch(n == 2 ? l : launch, n == 2 ? single : l);
+            if (rc) return rc;
+            // warm-up
+            for (int t = 0; t < 2; ++t)
+              if (enqueue_step(step, cur, n, stream, false)) return DUGKS_E_HIP;
+            e = hipEventRecord(ev0, stream);
+            for (int t = 0; t < trials && e == hipSuccess; ++t)
+              if (enqueue_step(step, cur, n, stream, false)) return DUGKS_E_HIP;
+            if (e == hipSuccess) e = hipEventRecord(ev1, stream);
+            if (e == hipSuccess) e = hipEventSynchronize(ev1);
+            float ms = 0;
+            if (e == hipSuccess) e = hipEventElapsedTime(&ms, ev0, ev1);
+            if (e != hipSuccess) return hipfail(e, "autotune timing");
+            if (ms < best_ms) { best_ms = ms; best = l; }
+          }
+      return DUGKS_OK;
+    };
+    Launch one, two;
+    int rc = fastest(1, one);
+    if (rc == DUGKS_OK && count == 2) rc = fastest(2, two);
+    if (rc == DUGKS_OK) rc = use_launch(count == 2 ? two : one, one);
     if (rc) return rc;
+    launch_chosen = true;
     for (size_t k = 0; k < inst.size(); ++k) {
       e = hipMemcpyAsync(ws + inst[k].off_slots, saved[k].data(), kSlots * sizeof(float),
                          hipMemcpyHostToDevice, stream);
@@ -1139,6 +1184,7 @@ size_t dugks_workspace_bytes(const dugks_ctx* ctx) {
   tmp_view.storage = ctx->storage;
   tmp_view.inst = ctx->inst;
   tmp_view.launch = ctx->launch;
+  tmp_view.single = ctx->single;
   tmp_view.layout();
   return tmp_view.total_bytes;
 }
@@ -1395,6 +1441,7 @@ size_t dugks_batch_workspace_bytes(const dugks_batch* b) {
   tmp_view.storage = b->storage;
   tmp_view.inst = b->inst;
   tmp_view.launch = b->launch;
+  tmp_view.single = b->single;
   tmp_view.layout();
   return tmp_view.total_bytes;
 }

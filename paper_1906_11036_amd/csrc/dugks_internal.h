@@ -95,6 +95,7 @@ struct Launch {
   int waves_per_block = 2;
   int schedule = DUGKS_SCHED_GRID;
   int xcd_remap = 1;
+  int half_edges = 0;   // waves beside walls march half the rows
 };
 
 // Kernel entry points (dugks_kernels.hip), all enqueued on `stream`; each

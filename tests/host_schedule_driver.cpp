@@ -191,9 +191,27 @@ static void captured() {
   if (captures) fail("captures", captures, 0);
 }
 
+// a caller's rows a wave are taken as given, beside walls too: one item for each
+// strip of 62 columns and chunk of so many rows
+static void chosen() {
+  for (int bc : {DUGKS_BC_PERIODIC, DUGKS_BC_MIRROR})
+    for (int storage = DUGKS_F64; storage <= DUGKS_BF16NEQ; ++storage) {
+      const int nx = 130, ny = 41;
+      Ctx c(storage, bc, bc, false, nx, ny);
+      for (int rows : {1, 3, 8, 41, 100}) {
+        c.must(dugks_set_launch(c.h, rows, 1, DUGKS_SCHED_GRID, 1));
+        dugks_info i;
+        dugks_get_info(c.h, &i);
+        const long long want = (long long)((nx + 61) / 62) * ((ny + rows - 1) / rows);
+        if (i.work_items != want) fail("work items", i.work_items, want);
+      }
+    }
+}
+
 int main() {
   runs();
   captured();
+  chosen();
   if (!fails) puts("ok");
   return fails ? 1 : 0;
 }
