@@ -267,6 +267,7 @@ struct Engine {
   std::vector<char> ready;
   long long step = 0;
   int cur = 0;   // the buffer that holds the state
+  int replay_buf = 0;   // the buffer that the replay table holds first
   bool need_measure = false;
   // graphs of kGraphSteps[0] and kGraphSteps[1] steps
   hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
@@ -574,6 +575,7 @@ struct Engine {
       e = hipMemcpyAsync((InstDev*)(ws + off_table) + t * inst.size(), host_table.data(), sizeof(InstDev) * inst.size(),
                          hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return hipfail(e, "upload instance table");
+    replay_buf = 0;
     e = upload_items();
     if (e != hipSuccess) return hipfail(e, "upload work list");
     for (auto& in : inst) {
@@ -790,9 +792,10 @@ struct Engine {
           int rc = build_graph(w);
           if (rc) return rc;
         }
-        if (launch_set_base(dev_table(), replay_table(), (int)inst.size(), cur,
+        if (launch_set_base(dev_table(), replay_table(), replay_buf == cur ? 0 : (int)inst.size(), cur,
                             (long long*)(ws + off_stepbase), step, stream))
           return fail(DUGKS_E_HIP, "step base launch failed");
+        replay_buf = cur;
         hipError_t e = hipGraphLaunch(graph_exec[w], stream);
         if (e != hipSuccess) return hipfail(e, "graph launch");
         step += kGraphSteps[w];

@@ -147,8 +147,9 @@ int launch_norms_noalloc(const InstDev* d, const InstDev& h, const double* ref, 
                          long long step, const double* widths, double* out_dev, void* stream);
 int launch_fill_u32(unsigned* p, unsigned v, long long n, void* stream);
 // Before a replay: base[0] = step (StepArgs::step_base), and the buffers of the n
-// instances of `replay` (read by the captured launches as from buffer 0) those of
-// `insts`, buffer `buf` first, so that one graph serves a state in either buffer.
+// (0: none) instances of `replay` (read by the captured launches as from buffer 0)
+// those of `insts`, buffer `buf` first, so that one graph serves a state in either
+// buffer.
 int launch_set_base(const InstDev* insts, InstDev* replay, int n, int buf, long long* base, long long step,
                     void* stream);
 

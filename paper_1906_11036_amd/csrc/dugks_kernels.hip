@@ -1967,7 +1967,7 @@ int launch_norms_noalloc(const InstDev* d, const InstDev& h, const double* ref, 
 
 int launch_set_base(const InstDev* insts, InstDev* replay, int n, int buf, long long* base, long long step,
                     void* stream) {
-  hipLaunchKernelGGL(k_set_base, dim3((n + 63) / 64), dim3(64), 0, S(stream), insts, replay, n, buf, base, step);
+  hipLaunchKernelGGL(k_set_base, dim3(n > 0 ? (n + 63) / 64 : 1), dim3(64), 0, S(stream), insts, replay, n, buf, base, step);
   DUGKS_CHECK_LAUNCH();
 }
 
