@@ -135,11 +135,28 @@ template <int ST> __host__ __device__ inline float neq_scale_for(float m) {
 // kSlotWays values (one address took the atomics of every wave of the instance:
 // 1024^2 bf16neq 24.5 us a step at its best launch, 15.4 spread; 700 x 333 in
 // 2004 waves 30 and 14.6).
+// The maximum is taken with DPP and read into a scalar: it and its scales are
+// wave-uniform, and shuffles would hold six lane addresses from the kernel's start
+// to its end (f16neq, D2Q9, 168 registers, 2 / 4 / 8 coefficients: 7 / 10 / 3 of
+// them spilled, 23 / 18 / 15 without the x <-> y symmetry; now 0 / 0 / 0 and 7 / 3
+// / 0; the batch of 256 instances takes 466 us a step either way).
+template <int CTRL> __device__ __forceinline__ float dpp_max(float v) {
+  return fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true)));
+}
+__device__ __forceinline__ float uniform(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ float wave_max(float v) {   // v >= 0 (a lane without a source reads 0); whole waves only
+  v = dpp_max<0x111>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row of 16 has the row's
+  v = dpp_max<0x112>(v);
+  v = dpp_max<0x114>(v);
+  v = dpp_max<0x118>(v);
+  v = dpp_max<0x142>(v);   // row_bcast:15, :31: lane 63 has the wave's
+  v = dpp_max<0x143>(v);
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
 __device__ __forceinline__ float slot_max(const InstDev* __restrict__ I, int slot) {   // whole waves only
-  float m = I->slots[slot * kSlotWays + (threadIdx.x & 63)];
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  return m;
+  return wave_max(I->slots[slot * kSlotWays + (threadIdx.x & 63)]);
 }
 static_assert(kSlotWays == 64, "one value a lane");
 
@@ -730,8 +747,8 @@ __device__ __forceinline__ void step_item(const InstDev* __restrict__ I, const W
   Scales sc{1.0f, 1.0f};
   if constexpr (Stor<ST>::neq) {
     if constexpr (ST == DUGKS_F16NEQ) {   // (bfloat16 is stored unscaled)
-      sc.inv_in = 1.0f / neq_scale_for<ST>(slot_max(I, (int)((step + 2) & 3)));
-      sc.out = neq_scale_for<ST>(slot_max(I, (int)((step + 3) & 3)));
+      sc.inv_in = uniform(1.0f / neq_scale_for<ST>(slot_max(I, (int)((step + 2) & 3))));
+      sc.out = uniform(neq_scale_for<ST>(slot_max(I, (int)((step + 3) & 3))));
     }
     // slot (step + 1) & 3, neither read nor written by this step, is cleared for
     // the next one by the instance's first item
@@ -1005,10 +1022,8 @@ __device__ __forceinline__ void step_item(const InstDev* __restrict__ I, const W
   bad = bad && live;
   ovf = ovf && live;
   if constexpr (Stor<ST>::neq) {
-    mx = live ? mx : 0.0f;
     // wave maximum of |f~_i - E_i| (i >= 1) over updated cells -> the instance's slot
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    mx = wave_max(live ? mx : 0.0f);
     // The waves spread over the slot's values.  (Reading the value first, to
     // leave atomics out, kept every wave waiting at its end: 0.03 ms a step of 64
     // instances in bf16neq.)
