@@ -1780,10 +1780,13 @@ int launch_step_q_st(const StepArgs& a, const Launch& l, void* stream, int measu
     DUGKS_STEP_NC(kSrcPow, false);
   } else if (a.src) {
     DUGKS_STEP_NC(1, false);
-  } else if (a.sym && ST == DUGKS_F32) {   // binary32 without a source: a little faster too
-    DUGKS_STEP_NC(0, true);
   } else {
-    DUGKS_STEP_NC(0, false);
+    bool sym = false;
+    if constexpr (ST == DUGKS_F32) {   // binary32 without a source: a little faster too
+      sym = a.sym;
+      if (sym) DUGKS_STEP_NC(0, true);
+    }
+    if (!sym) DUGKS_STEP_NC(0, false);
   }
 #undef DUGKS_STEP_NC
 #undef DUGKS_STEP_LAUNCH
@@ -1806,19 +1809,19 @@ int launch_step2_q_st(const StepArgs& a, const Launch& l, void* stream) {
 #define DUGKS_STEP2_LAUNCH(NC_, SYM_)                                                                            \
   hipLaunchKernelGGL((k_step2<Q, ST, NC_, SYM_>), grid, block, 0, S(stream), a.insts, a.items, a.nitems, a.parity, \
                      a.step, l.xcd_remap, persistent, a.step_base)
-    if (a.sym && ST == DUGKS_F32) {
-      switch (a.ncoef) {
-        case 2: DUGKS_STEP2_LAUNCH(2, true); break;
-        case 4: DUGKS_STEP2_LAUNCH(4, true); break;
-        default: DUGKS_STEP2_LAUNCH(8, true); break;
-      }
-    } else {
-      switch (a.ncoef) {
-        case 2: DUGKS_STEP2_LAUNCH(2, false); break;
-        case 4: DUGKS_STEP2_LAUNCH(4, false); break;
-        default: DUGKS_STEP2_LAUNCH(8, false); break;
-      }
+#define DUGKS_STEP2_NC(SYM_)                          \
+  switch (a.ncoef) {                                  \
+    case 2: DUGKS_STEP2_LAUNCH(2, SYM_); break;       \
+    case 4: DUGKS_STEP2_LAUNCH(4, SYM_); break;       \
+    default: DUGKS_STEP2_LAUNCH(8, SYM_); break;      \
+  }
+    bool sym = false;
+    if constexpr (ST == DUGKS_F32) {
+      sym = a.sym;
+      if (sym) DUGKS_STEP2_NC(true)
     }
+    if (!sym) DUGKS_STEP2_NC(false)
+#undef DUGKS_STEP2_NC
 #undef DUGKS_STEP2_LAUNCH
     DUGKS_CHECK_LAUNCH();
   }
