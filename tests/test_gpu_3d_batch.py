@@ -70,6 +70,34 @@ def test_batch_equals_instances_alone(storage, launch, q, specs):
     b.close()
 
 
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("specs", [
+    [(70, 9, 41, (P, P, P), 1), (33, 5, 3, (M, P, M), 2), (20, 13, 1, (D, M, P), 2)],
+    [(25, 6, 131, (P, P, P), 1), (64, 4, 17, (M, M, M), 1)]])
+def test_default_launch_of_a_batch(storage, specs):
+    """Without a launch the planes a block come from the meshes' sizes (an even split
+    of the tallest one): meshes much shorter than the tallest, more than 128
+    planes, walls; bitwise the instances alone at the reported launch."""
+    probs = members(19, specs, 1240)
+    say(f"case 3-D batch default launch {storage} sizes {[s[:3] for s in specs]}")
+    steps = 3
+    solvers = []
+    for p in probs:
+        s = dg.Solver3D(p, storage=storage)
+        s.set_phi(p.phi0)
+        if D in p.bc:
+            s.set_dirichlet(p.rings(steps))
+        solvers.append(s)
+    b = dg.Batch3D(solvers)
+    inf = b.info()
+    launch = (inf["rows_per_block"], inf["planes_per_block"])
+    assert 1 <= launch[1] <= 128
+    b.step(steps)
+    for p, s in zip(probs, solvers):
+        assert np.array_equal(s.get_f(), run_alone(p, storage, steps, launch)), (p.nx, p.ny, p.nz, p.bc)
+    b.close()
+
+
 def test_batch_refuses_unequal_steps_and_sources():
     probs = members(19, [(30, 6, 5, (P, P, P), 1), (25, 7, 4, (P, P, P), 1)], 1300)
     solvers = [dg.Solver3D(p, storage="f64") for p in probs]
