@@ -236,7 +236,9 @@ struct dugks3_ctx {
     // equilibrium coefficients or with D3Q7's source
     const bool walls = p.bc[0] != DUGKS_BC_PERIODIC || p.bc[1] != DUGKS_BC_PERIODIC ||
                        p.bc[2] != DUGKS_BC_PERIODIC || ncoef > 4 || (q == 7 && src_n > 0);
-    return step3_lds_bytes(p.storage, q, walls, l, src_n > 0);
+    // source terms that the instantiation has room for
+    const int src = src_n == 0 ? 0 : (q != 7 && ncoef <= 4 && src_n <= 2 ? 2 : DUGKS_MAX_SRC_TERMS);
+    return step3_lds_bytes(p.storage, q, walls, l, src);
   }
   size_t lds_limit() const {
     int dev = 0, v = 65536;

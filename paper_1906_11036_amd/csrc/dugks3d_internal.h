@@ -104,8 +104,9 @@ int launch_step3_batch(const Batch3& bt, const Inst3& h, int parity, bool walls,
                        const Launch3& l, void* stream);
 // LDS bytes of one block of the step kernel (walls: the instantiation with
 // mirror code, for a non-periodic axis or more than four coefficients)
-// src: the source instantiation (D3Q7 then runs the staged kernel too)
-size_t step3_lds_bytes(int storage, int q, bool walls, const Launch3& l, bool src = false);
+// src: the source terms that the instantiation has room for, 0 without a source
+// (D3Q7 with one runs the staged kernel too)
+size_t step3_lds_bytes(int storage, int q, bool walls, const Launch3& l, int src = 0);
 int launch_init3(const Inst3* d, const Inst3& h, const double* phi, int parity, void* stream);
 int launch_set_f3(const Inst3* d, const Inst3& h, const double* f, int parity, void* stream);
 int launch_get_phi3(const Inst3* d, const Inst3& h, double* out, int parity, long long step, void* stream);

@@ -885,21 +885,27 @@ template <int Q> __host__ __device__ constexpr int half_of(int k) {
   if (Q == 15) return nnz == 3 ? 1 : 0;                              // 7 + 8
   return (x == 0 && nnz == 1) ? 1 : 0;                               // 3 + 4
 }
-// Binary32 with 3 or more rows splits each row four ways.  D3Q19: {rest,
+// Binary32 with 3 or more rows (2 without a source) splits each row four ways.  D3Q19: {rest,
 // (+-1,+-1,0)}, {(+-1,0,+-1)}, {(0,+-1,+-1)}, {axis directions}, closed
 // under the wall mirrors.  D3Q15 only without walls (a z mirror moves a
 // corner between the last two): {rest, +-x}, {+-y, +-z}, {corners with
 // c_z = +1}, {corners with c_z = -1}.  Each half is two quarters.
-// Binary64 at 2 rows does the same.
-template <int Q, typename T, int ROWS, bool WALLS> constexpr int parts() {
+// Binary64 at 2 rows does the same.  (Two rows with a source: 128^3 with mirror
+// walls and one term 317 us a step in two parts, 396 in four.)
+template <int Q, typename T, int ROWS, bool WALLS, int SRC> constexpr int parts() {
   constexpr bool quarters = Q == 19 || (Q == 15 && !WALLS);
-  return (quarters && ((sizeof(T) == 4 && ROWS >= 2) || (sizeof(T) == 8 && ROWS == 2))) ? 4 : 2;
+  return (quarters && ((sizeof(T) == 4 && ROWS >= (SRC > 0 ? 3 : 2)) || (sizeof(T) == 8 && ROWS == 2))) ? 4 : 2;
 }
 // rows of raw f~ staged in LDS: the tile's rows and its two halo rows, or, with
 // four waves a row, none: each wave loads its quarter of its row (and of the
-// halo row that it makes) into registers, two planes ahead
-template <int Q, typename T, int ROWS, bool WALLS> constexpr int staged_rows() {
-  return parts<Q, T, ROWS, WALLS>() == 4 ? 0 : ROWS + 2;
+// halo row that it makes) into registers, two planes ahead.  Binary32 with 4 rows,
+// mirror code and room for any number of source terms has 128 registers and no
+// room for that (46 to 60 spilled): it stages the tile's rows and loads its quarter
+// of a halo row one plane ahead (128^3 with mirror walls, us a step: four terms 433
+// -> 394; one term and more than four coefficients 415 -> 358).
+template <int Q, typename T, int ROWS, bool WALLS, int SRC> constexpr int staged_rows() {
+  if (parts<Q, T, ROWS, WALLS, SRC>() != 4) return ROWS + 2;
+  return sizeof(T) == 4 && ROWS == 4 && WALLS && SRC > 2 ? ROWS : 0;
 }
 template <int Q, int P> __host__ __device__ constexpr int part_of(int k) {
   if (P == 2) return half_of<Q>(k);
@@ -1024,27 +1030,32 @@ __device__ __forceinline__ void face_out_src(const Inst3* __restrict__ I, const 
 
 // LDS bytes of a block with ns staging slots, the quarters' phi sums (binary64,
 // when raw f~ goes through registers) included (E coefficients aside)
-template <int Q, int ROWS, typename T, bool WALLS> constexpr int lds_p_bytes(int ns) {
-  return 3 * (ROWS + 2) * Q * kLanes * (int)sizeof(T) + ns * staged_rows<Q, T, ROWS, WALLS>() * Q * kLanes * (int)sizeof(T) +
-         4 * ROWS * parts<Q, T, ROWS, WALLS>() * kLanes * (int)sizeof(T) +
-         (staged_rows<Q, T, ROWS, WALLS>() == 0 ? (ROWS + 2) * 4 * kLanes * 8 : 0);
+template <int Q, int ROWS, typename T, bool WALLS, int SRC> constexpr int lds_p_bytes(int ns) {
+  return 3 * (ROWS + 2) * Q * kLanes * (int)sizeof(T) + ns * staged_rows<Q, T, ROWS, WALLS, SRC>() * Q * kLanes * (int)sizeof(T) +
+         4 * ROWS * parts<Q, T, ROWS, WALLS, SRC>() * kLanes * (int)sizeof(T) +
+         (staged_rows<Q, T, ROWS, WALLS, SRC>() == 0      ? (ROWS + 2) * 4 * kLanes * 8
+          : staged_rows<Q, T, ROWS, WALLS, SRC>() == ROWS ? 2 * 4 * kLanes * 8
+                                                          : 0);
 }
-template <int Q, int ROWS, typename T, bool WALLS> struct LdsP {
+template <int Q, int ROWS, typename T, bool WALLS, int SRC> struct LdsP {
   static constexpr int W = ROWS + 2;             // LDS rows: y0-1 .. y0+ROWS
   static constexpr int WD = sizeof(T) / 4;       // words per element
   // staging slots: binary32 two, unless one slot lets two blocks share a
   // CU's 160 KiB where two slots would not; binary64 one
   static constexpr int NS = WD == 2 ? 1
-                            : (lds_p_bytes<Q, ROWS, T, WALLS>(2) > 81920 && lds_p_bytes<Q, ROWS, T, WALLS>(1) <= 81920)
+                            : (lds_p_bytes<Q, ROWS, T, WALLS, SRC>(2) > 81920 && lds_p_bytes<Q, ROWS, T, WALLS, SRC>(1) <= 81920)
                                   ? 1
                                   : 2;
-  // E coefficients in vector registers (from LDS) with two slots or none
-  static constexpr int RR = staged_rows<Q, T, ROWS, WALLS>();
+  // E coefficients in vector registers (from LDS) with two slots, or with none and
+  // no source, which fills them
+  static constexpr int RR = staged_rows<Q, T, ROWS, WALLS, SRC>();
   static constexpr bool kReg = RR == 0;          // raw f~ loaded into registers
-  static constexpr bool kVecE = WD == 1 && (NS == 2 || kReg);
+  static constexpr bool kHalo = RR == ROWS;      // the halo rows' alone, one plane ahead
+  static_assert(!kHalo || NS == 2, "the halo rows' pipeline takes two slots");
+  static constexpr bool kVecE = WD == 1 && (kReg ? SRC == 0 : NS == 2);
   T gsl[3][W][Q][kLanes];                        // g of plane p in slot (p - z0) mod 3
   unsigned raw[kReg ? 0 : NS][RR][Q][WD][kLanes];   // staged f~, binary64 as low and high words (none: no bytes)
-  T psum[4][ROWS][parts<Q, T, ROWS, WALLS>()][kLanes];   // the parts' interface-g sums of four faces
+  T psum[4][ROWS][parts<Q, T, ROWS, WALLS, SRC>()][kLanes];   // the parts' interface-g sums of four faces
 };
 
 // One wave: row rw of the tile, directions of half H.
@@ -1059,17 +1070,17 @@ template <int Q, int ROWS, typename T, bool WALLS> struct LdsP {
 template <int Q, int NC, int ROWS, typename T, int H, bool WALLS, int SRC>
 __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int parity,
                                             const double* __restrict__ ring, STab tb, int planes,
-                                            int strips, int tiles, LdsP<Q, ROWS, T, WALLS>& L,
+                                            int strips, int tiles, LdsP<Q, ROWS, T, WALLS, SRC>& L,
                                             const float* ecoef, double (*qphi)[4][kLanes], double (*afs)[ROWS + 2][4][kLanes],
                                             int w, int rw,
                                             int blk) {
-  using LP = LdsP<Q, ROWS, T, WALLS>;
-  constexpr int P = parts<Q, T, ROWS, WALLS>();
+  using LP = LdsP<Q, ROWS, T, WALLS, SRC>;
+  constexpr int P = parts<Q, T, ROWS, WALLS, SRC>();
   constexpr int W = LP::W, WD = LP::WD;
   constexpr int NW = P * ROWS;                   // waves per block
   constexpr int HX = (2 * Q + NW - 1) / NW;      // halo-row loads per wave
   constexpr unsigned ES = sizeof(T);
-  constexpr bool kVecE = LP::kVecE && NC <= 4 && !(SRC > 0 && LP::kReg);
+  constexpr bool kVecE = LP::kVecE && NC <= 4;
   const int lane = threadIdx.x & 63;
   int b = blk;   // the block within its instance
   const int sx = b % strips;
@@ -1121,7 +1132,7 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
   };
   // kReg: raw f~ of this wave's quarter of its row and, for the waves of rows 0
   // and 1, of the halo row that they make
-  T RW[LP::kReg ? 2 : 1][LP::kReg ? Q : 1], HR[LP::kReg ? 2 : 1][LP::kReg ? Q : 1];
+  T RW[LP::kReg ? 2 : 1][LP::kReg ? Q : 1], HR[LP::kReg ? 2 : 1][LP::kReg || LP::kHalo ? Q : 1];
   auto load_part = [&](T* v, unsigned o) __attribute__((always_inline)) {
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
@@ -1139,24 +1150,29 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
     load_part(RW[S], cell_index(srow, zp) * ES);
     if (rw <= 1) load_part(HR[S], cell_index(rw == 0 ? slo : shi, zp) * ES);
   };
-  // the quarter sums of the cells' phi of a loaded plane, to LDS
+  // the quarter sums of the cells' phi of a loaded plane, to LDS (qphi's rows are
+  // the LDS rows, or the two halo rows)
+  auto quarter_sum = [&](const T* v) __attribute__((always_inline)) {
+    double q = 0.0;
+#pragma unroll
+    for (int k = 0; k < Q; ++k)
+      if (part_of<Q, P>(k) == H) q += (double)v[k];
+    return q;
+  };
   auto phi_sums = [&](auto sc) __attribute__((always_inline)) {
     constexpr int S = decltype(sc)::value;
-    auto sum = [&](const T* v) __attribute__((always_inline)) {
-      double q = 0.0;
-#pragma unroll
-      for (int k = 0; k < Q; ++k)
-        if (part_of<Q, P>(k) == H) q += (double)v[k];
-      return q;
-    };
-    qphi[me][H][lane] = sum(RW[S]);
-    if (rw <= 1) qphi[rw == 0 ? 0 : W - 1][H][lane] = sum(HR[S]);
+    qphi[me][H][lane] = quarter_sum(RW[S]);
+    if (rw <= 1) qphi[rw == 0 ? 0 : W - 1][H][lane] = quarter_sum(HR[S]);
   };
-  // two parts a row: stage plane zp, this wave's directions of its row and its
-  // share of the two halo rows (offsets advance in a vector register)
+  auto halo_sums = [&]() __attribute__((always_inline)) {
+    if constexpr (LP::kHalo)
+      if (rw <= 1) qphi[rw][H][lane] = quarter_sum(HR[0]);
+  };
+  // stage plane zp: this wave's directions of its row and its share of the two halo
+  // rows (offsets advance in a vector register)
   auto stage = [&](int slot, int zp) __attribute__((always_inline)) {
     unsigned o = cell_index(srow, zp) * ES;
-    const int wme = me;
+    const int wme = LP::kHalo ? me - 1 : me;
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
       if (part_of<Q, P>(k) == H) {
@@ -1165,6 +1181,10 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
           __builtin_amdgcn_raw_ptr_buffer_load_lds(Rin, LDS_PTR(&L.raw[slot][wme][k][h][0]), 4, o + 4u * h, 0, 0, 0);
       }
       o += planeB;
+    }
+    if constexpr (LP::kHalo) {
+      if (rw <= 1) load_part(HR[0], cell_index(rw == 0 ? slo : shi, zp) * ES);
+      return;
     }
     const unsigned ilo = cell_index(slo, zp) * ES, ihi = cell_index(shi, zp) * ES;
     const int j0 = w * HX;
@@ -1183,11 +1203,12 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
   };
   // staged raw f~ of LDS row `row`
   auto raw_at = [&](int slot, int row, int k) __attribute__((always_inline)) -> T {
+    const int rr = LP::kHalo ? row - 1 : row;
     if constexpr (WD == 1)
-      return __builtin_bit_cast(float, L.raw[slot][row][k][0][lane]);
+      return __builtin_bit_cast(float, L.raw[slot][rr][k][0][lane]);
     else
-      return __builtin_bit_cast(double, (unsigned long long)L.raw[slot][row][k][0][lane] |
-                                            ((unsigned long long)L.raw[slot][row][k][1][lane] << 32));
+      return __builtin_bit_cast(double, (unsigned long long)L.raw[slot][rr][k][0][lane] |
+                                            ((unsigned long long)L.raw[slot][rr][k][1][lane] << 32));
   };
   // g = fbar+ / b1 (eq. 2.21 over b1) of this half's directions; phi (binary64) from all of them
   // (halo: with raw f~ in registers, the halo row's values in HR)
@@ -1212,6 +1233,11 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
       for (int k = 0; k < Q; ++k)
         if (part_of<Q, P>(k) == H) f[k] = decltype(halo)::value ? HR[slot][k] : RW[slot][k];
       phi = (qphi[row][0][lane] + qphi[row][1][lane]) + (qphi[row][2][lane] + qphi[row][3][lane]);
+    } else if constexpr (LP::kHalo && decltype(halo)::value) {   // rw: 0 the lower halo row, 1 the upper
+#pragma unroll
+      for (int k = 0; k < Q; ++k)
+        if (part_of<Q, P>(k) == H) f[k] = HR[0][k];
+      phi = (qphi[rw][0][lane] + qphi[rw][1][lane]) + (qphi[rw][2][lane] + qphi[rw][3][lane]);
     } else {
       double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -1371,6 +1397,21 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
     load_plane(R0{}, z0 + 2 < z1 ? z0 + 2 : z1);
     load_gs(z0 + 1);
     lds_barrier();
+  } else if constexpr (LP::kHalo) {   // one plane of halo registers: planes one at a time
+    stage(1, z0 - 1);
+    wait_vm_all();
+    halo_sums();
+    lds_barrier();
+    load_ecoef();
+    plane_g(R1{}, z0 - 1, 2, G1, FT1, AF1);
+    lds_barrier();
+    stage(0, z0);
+    wait_vm_all();
+    halo_sums();
+    lds_barrier();
+    plane_g(R0{}, z0, 0, G0, O, AF0);
+    lds_barrier();
+    stage(1, z0 + 1);   // z1 >= z0 + 1
   } else if constexpr (two) {
     stage(1, z0 - 1);
     stage(0, z0);
@@ -1427,6 +1468,7 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
   }
   if constexpr (LP::kReg) phi_sums(R1{});   // plane z0+1
   else wait_vm_all();
+  halo_sums();
   lds_barrier();
   if constexpr (kSolve) {
     solve_cells(1);
@@ -1523,6 +1565,7 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
     }
     if constexpr (LP::kReg) phi_sums(std::integral_constant<int, 1 - RS>{});   // plane z+2
     else wait_vm_all();   // this wave's loads of plane z+2 (and its older stores) are done
+    if (z + 2 <= z1) halo_sums();
     // the parts' sums and the whole staged plane z+2 are in LDS; slot sm
     // (read only above) is free for the next plane's g
     lds_barrier();
@@ -1646,12 +1689,12 @@ __device__ __forceinline__ void step3p_half(const Inst3* __restrict__ I, int par
 // WALLS = false: every axis periodic, no mirror code
 // BATCH: the blocks of many instances (Batch3) in one launch
 template <int Q, int NC, int ROWS, typename T, bool WALLS, int SRC, bool BATCH>
-__global__ __launch_bounds__((64 * parts<Q, T, ROWS, WALLS>() * ROWS)) void k_step3p(const Inst3* __restrict__ I, int parity,
+__global__ __launch_bounds__((64 * parts<Q, T, ROWS, WALLS, SRC>() * ROWS)) void k_step3p(const Inst3* __restrict__ I, int parity,
                                                                        const double* __restrict__ ring,
                                                                        const SrcTab st, int planes, int strips,
                                                                        int tiles, const Batch3 bt) {
-  constexpr int P = parts<Q, T, ROWS, WALLS>();
-  __shared__ LdsP<Q, ROWS, T, WALLS> L;
+  constexpr int P = parts<Q, T, ROWS, WALLS, SRC>();
+  __shared__ LdsP<Q, ROWS, T, WALLS, SRC> L;
   int blk = xcd_contiguous(blockIdx.x, gridDim.x);
   if constexpr (BATCH) {   // this block's instance: the last k with first[k] <= blk
     int lo = 0, hi = bt.n - 1;
@@ -1672,7 +1715,7 @@ __global__ __launch_bounds__((64 * parts<Q, T, ROWS, WALLS>() * ROWS)) void k_st
   // (waves w, w+4, ...) runs every part once
   const int part = P == 2 ? (w & 1) : ((w + rw) & 3);
   const float* ec = nullptr;
-  if constexpr (LdsP<Q, ROWS, T, WALLS>::kVecE && NC <= 4) {
+  if constexpr (LdsP<Q, ROWS, T, WALLS, SRC>::kVecE && NC <= 4) {
     __shared__ float ecoef[Q * NC];   // E_i coefficients, read into vector registers
     if (w == 0)
       for (int i = threadIdx.x; i < Q * NC; i += kLanes) ecoef[i] = I->ef[i / NC][i % NC];
@@ -1680,12 +1723,15 @@ __global__ __launch_bounds__((64 * parts<Q, T, ROWS, WALLS>() * ROWS)) void k_st
   }
   const STab tb = &st;
   double (*hp)[4][kLanes] = nullptr;
-  if constexpr (LdsP<Q, ROWS, T, WALLS>::kReg) {
+  if constexpr (LdsP<Q, ROWS, T, WALLS, SRC>::kReg) {
     __shared__ double qphi[ROWS + 2][4][kLanes];   // quarter sums of the cells' phi of a plane's rows
+    hp = qphi;
+  } else if constexpr (LdsP<Q, ROWS, T, WALLS, SRC>::kHalo) {
+    __shared__ double qphi[2][4][kLanes];          // of its two halo rows
     hp = qphi;
   }
   double (*afs)[ROWS + 2][4][kLanes] = nullptr;
-  if constexpr (SRC > 0 && LdsP<Q, ROWS, T, WALLS>::kReg && sizeof(T) == 4) {
+  if constexpr (SRC > 0 && LdsP<Q, ROWS, T, WALLS, SRC>::kReg && sizeof(T) == 4) {
     __shared__ double af[3][ROWS + 2][4][kLanes];   // the cells' face coefficients of three planes
     afs = af;
   }
@@ -1900,7 +1946,7 @@ static void step3_row_waves(const Inst3* d, const Inst3& h, int parity, const do
 
 template <int Q, int NC, int ROWS, typename T, bool WALLS, int SRC, bool BATCH>
 static void step3p_go(const Args3& a, const Launch3& l, dim3 grid, hipStream_t st) {
-  hipLaunchKernelGGL((k_step3p<Q, NC, ROWS, T, WALLS, SRC, BATCH>), grid, dim3(64 * parts<Q, T, ROWS, WALLS>() * ROWS),
+  hipLaunchKernelGGL((k_step3p<Q, NC, ROWS, T, WALLS, SRC, BATCH>), grid, dim3(64 * parts<Q, T, ROWS, WALLS, SRC>() * ROWS),
                      0, st, a.d, a.parity, a.ring, a.ss, l.planes, a.strips, a.tiles, a.bt);
 }
 template <int Q, int NC, typename T, bool WALLS, int SRC, bool BATCH = false>
@@ -2004,19 +2050,19 @@ int launch_step3_batch(const Batch3& bt, const Inst3& h, int parity, bool walls,
   }
 }
 
-size_t step3_lds_bytes(int storage, int q, bool walls, const Launch3& l, bool src) {
+size_t step3_lds_bytes(int storage, int q, bool walls, const Launch3& l, int src) {
   if (q == 7 && !src)   // binary64: g of 3 planes (dynamic); binary32: g of 3 planes and f~ of 2
     return storage == DUGKS_F64 ? step3h_lds_bytes(q, l) : (size_t)5 * (l.rows + 2) * q * kLanes * 4;
   // g of 3 planes and staged f~ of 1 or 2 planes (LdsP), each of rows + 2
   // rows, and the parts' sums of 4 faces per row (static; the binary32 E
   // coefficients aside)
   const size_t e = storage == DUGKS_F64 ? 8 : 4;
-  // parts<Q, T, ROWS, WALLS>(), walls meaning the instantiation with mirror code
+  // parts<>() and staged_rows<>(), walls meaning the instantiation with mirror code
   const bool quarters = q == 19 || (q == 15 && !walls);
-  const size_t np = (quarters && ((storage != DUGKS_F64 && l.rows >= 2) || (storage == DUGKS_F64 && l.rows == 2))) ? 4 : 2;
-  const size_t rr = np == 4 ? 0 : l.rows + 2;   // staged_rows<>()
-  const size_t as = src && np == 4 && e == 4 ? (size_t)3 * (l.rows + 2) * 4 * kLanes * 8 : 0;   // face coefficients
-  const size_t hs = rr == 0 ? (size_t)(l.rows + 2) * 4 * kLanes * 8 : 0;        // quarters' phi sums
+  const size_t np = (quarters && ((e == 4 && l.rows >= (src > 0 ? 3 : 2)) || (e == 8 && l.rows == 2))) ? 4 : 2;
+  const size_t rr = np != 4 ? l.rows + 2 : (e == 4 && l.rows == 4 && walls && src > 2) ? l.rows : 0;
+  const size_t as = src > 0 && rr == 0 && e == 4 ? (size_t)3 * (l.rows + 2) * 4 * kLanes * 8 : 0;   // face coefficients
+  const size_t hs = (size_t)(rr == 0 ? l.rows + 2 : (int)rr == l.rows ? 2 : 0) * 4 * kLanes * 8;   // quarters' phi sums
   auto bytes = [&](size_t ns) {
     return as + 3 * (l.rows + 2) * q * kLanes * e + ns * rr * q * kLanes * e + (size_t)4 * l.rows * np * kLanes * e + hs;
   };
