@@ -412,11 +412,12 @@ struct Engine {
     for (auto& in : inst) n += count_items(in, l, cols);
     return n;
   }
-  bool any_wall() const {
+  bool any_wall(int bc) const {
     for (auto& in : inst)
-      if (in.bcx != DUGKS_BC_PERIODIC || in.bcy != DUGKS_BC_PERIODIC) return true;
+      if (in.bcx == bc || in.bcy == bc) return true;
     return false;
   }
+  bool any_wall() const { return any_wall(DUGKS_BC_DIRICHLET) || any_wall(DUGKS_BC_MIRROR); }
   // The launch of one or two steps when the caller has not chosen.  Rows a wave
   // marches: a SIMD runs k = waves / 1024 of them, each H rows and a prologue
   // worth c rows, and more than one at a time only fills the gaps of a row's
@@ -430,13 +431,16 @@ struct Engine {
   // Beside walls a launch of one step may also leave the rows whole, for which the
   // waves there end a little later: 0.15 (H + c) more.  us a step, whole and
   // halved: 1024^2 binary64 33.5 and 31.2 (20 rows), 2048^2 binary32 80 and 90
-  // (24), 1400^2 binary64 67 and 85 (32), 4096^2 binary64 552 and 590 (32).
+  // (24), 1400^2 binary64 67 and 85 (32), 4096^2 binary64 552 and 590 (32).  Dirichlet
+  // data make that 0.5, but in binary32: 2048^2, whole and halved, binary64 153 (24)
+  // and 147 (20), bf16neq 50 (24) and 46 (20), binary32 83 (12) and 89 (20).
   // Blocks of 4 waves (binary64: 2) once they fill the chip several times over,
   // single waves before (they spread over more CUs).
   Launch default_of(bool two) const {
     const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48};
     const double v = storage == DUGKS_F64 ? 1.0 : 0.75, c = two ? 3.5 : 2.5;
     const int cols = two ? kStripCols2 : kStripCols;
+    const double late = storage != DUGKS_F32 && any_wall(DUGKS_BC_DIRICHLET) ? 0.5 : 0.15;
     double best_cost = 0;
     Launch best;
     for (int H : cand)
@@ -447,7 +451,7 @@ struct Engine {
         const double k = count_items(l, cols) / 1024.0;
         double load = v * (k < 8 ? std::ceil(k) : k);
         if (!two && storage == DUGKS_F32 && k < 8 && (int)std::ceil(k) % 2 == 1) load += 0.25;
-        const double cost = (std::max(1.0, load) + (half ? 0.0 : 0.15)) * (H + c);
+        const double cost = (std::max(1.0, load) + (half ? 0.0 : late)) * (H + c);
         if (best_cost == 0 || cost <= best_cost) { best_cost = cost; best = l; }
       }
     const double waves = count_items(best, kStripCols);
