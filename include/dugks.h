@@ -131,7 +131,8 @@ typedef struct dugks_info {
   int schedule;
   int xcd_remap;
   long long work_items;
-  size_t state_bytes;     /* bytes of one f~ buffer (read once and written once per step) */
+  size_t state_bytes;     /* bytes of one f~ buffer (read once and written once per launch,
+                             which takes one step or two: dugks_step) */
   long long graph_steps;  /* steps replayed from captured hipGraphs since dugks_bind */
   long long eager_steps;  /* steps launched outside graphs since dugks_bind */
   int xy_symmetric;       /* 1: E_i and E_j have bitwise the same coefficients for every pair
@@ -238,7 +239,8 @@ int dugks_set_f(dugks_ctx* ctx, const double* f, int on_device);
 
 /* Advance nsteps >= 0 steps, asynchronously on the bound stream.  A run that
  * holds four or more steps from a step divisible by 4 replays captured
- * hipGraphs of 32 and 4 steps from there (captured on first use on a stream of
+ * hipGraphs of 32 and 4 steps from there (unless fewer than 64 steps would
+ * split a pair for it; captured on first use on a stream of
  * the library's own, launched on the bound stream after a small kernel that
  * writes the first step's index, from which the captured kernels take the time
  * of their Dirichlet data and sources, and the instances' buffers to the

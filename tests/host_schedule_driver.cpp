@@ -147,8 +147,8 @@ struct Ctx {
 
 // Runs of every length from every phase: a chain of launches, each reading what
 // the one before wrote; two steps a launch wherever a run has two steps left;
-// graphs where a run holds four steps from a step divisible by 4, captured at
-// most once for each length.
+// graphs where a run holds four steps from a step divisible by 4 (and a short one
+// need not split a pair for them), captured at most once for each length.
 static void runs() {
   for (int storage = DUGKS_F64; storage <= DUGKS_BF16NEQ; ++storage)
     for (int kind = 0; kind < 3; ++kind) {   // periodic; Dirichlet data is not needed for mirror walls; a source
@@ -166,7 +166,8 @@ static void runs() {
         const int l = c.step(n);
         dugks_get_info(c.h, &b);
         const int lead = (int)((4 - done % 4) % 4);
-        const int in_graphs = n >= lead + 4 ? (n - lead) / 4 * 4 : 0;
+        const bool splits = pairs && lead % 2 == 1 && n % 2 == 0 && n < lead + 64;   // a pair, for a graph
+        const int in_graphs = n >= lead + 4 && !splits ? (n - lead) / 4 * 4 : 0;
         if (b.graph_steps - a.graph_steps != in_graphs) fail("steps in graphs", b.graph_steps - a.graph_steps, in_graphs);
         const int rest = in_graphs ? n - lead - in_graphs : n;
         const int want = !pairs ? n : in_graphs / 2 + (rest + 1) / 2 + (in_graphs ? (lead + 1) / 2 : 0);
