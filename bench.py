@@ -34,7 +34,8 @@ BYTES_PER_UPDATE = {0: 144, 1: 72, 2: 40, 3: 40}   # D2Q9: read + write of the s
 def bytes_per_update(storage, q):
     """Algorithmic bytes of one cell update: the stored state read and written
     once (binary64 / binary32: q values; 16-bit: phi in binary32 and q-1
-    scaled non-equilibrium values in 16 bits)."""
+    scaled non-equilibrium values in 16 bits); a launch moves as much for all
+    the steps that it takes."""
     per = {0: 8 * q, 1: 4 * q}.get(storage, 4 + 2 * (q - 1))
     return 2 * per
 
@@ -46,8 +47,16 @@ def source_terms(p):
     return 1 if getattr(p, "src_g", None) is not None else 0
 
 
+def steps_per_launch(problems, storage):
+    """Steps that one launch takes in a run: two in binary64 and binary32 storage
+    without a source, except where a Dirichlet axis stands beside a periodic one."""
+    from paper_1906_11036_amd import _lib as L
+    mixed = any({int(p.bcx), int(p.bcy)} == {L.BC_DIRICHLET, L.BC_PERIODIC} for p in problems)
+    return 2 if storage in (L.F64, L.F32) and not mixed and not any(source_terms(p) for p in problems) else 1
+
+
 def algorithmic_bytes(problems, storage):
-    """Algorithmic HBM bytes of one step over all problems: the state read and
+    """Algorithmic HBM bytes of one launch over all problems: the state read and
     written once, plus each source term's G read once."""
     return sum((bytes_per_update(storage, p.q) + 8 * source_terms(p)) * p.cells for p in problems)
 
@@ -269,6 +278,7 @@ def cpu_baseline3d(seconds, all_cores=True, sources=False):
 
 BYTES_PER_UPDATE3 = {0: 2 * 19 * 8, 1: 2 * 19 * 4}   # D3Q19: read + write of the stored state
 BYTES_PER_UPDATE1 = {0: 2 * 4 * 8, 1: 2 * 4 * 4}     # D1Q3: f~ (3) and phi^{n-1}, read + write
+STEPS_PER_LAUNCH1 = 4   # the one-dimensional kernel's, in runs of four or more
 
 
 def cpu_baseline1d(seconds):
@@ -320,7 +330,8 @@ def main1d(args):
     info = s.info()
     ms_step = ms / args.steps
     mlups = p.cells * args.steps / (ms * 1e-3) / 1e6
-    achieved = BYTES_PER_UPDATE1[storage] * p.cells / (ms_step * 1e-3) / 1e9
+    ms_launch = ms_step * STEPS_PER_LAUNCH1   # the state is read and written once a launch
+    achieved = BYTES_PER_UPDATE1[storage] * p.cells / (ms_launch * 1e-3) / 1e9
     log(f"{args.storage}: {ms_step:.4f} ms/step, {mlups:.0f} MLUPS, {achieved:.0f} GB/s algorithmic")
     extras = {}
     if not args.no_extras:
@@ -337,7 +348,7 @@ def main1d(args):
         extras = {"fp64_fused_mlups": round(fused64, 1), "rel_l2_vs_fp64": l2,
                   "rel_l2_after_steps": args.warmup + args.steps}
     kname = "k_step1"
-    traffic_b = measured_traffic(args.workload, args.storage, "one wave per 62 cells, 16 waves a block",
+    traffic_b = measured_traffic(args.workload, args.storage, "four steps a launch, one wave per 56 cells, 16 waves a block",
                                  kernel=kname, sources=("dugks1d.hip",))
     out = {
         "metric": METRIC, "value": round(mlups, 1), "unit": "MLUPS", "n_gpus": 1,
@@ -345,11 +356,12 @@ def main1d(args):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": args.storage, "data": "synthetic",
         "config": {"workload": args.workload, "instances": 1, "cells": p.cells, "lattice": "D1Q3",
-                   "storage": args.storage, "state_bytes": info["state_bytes"]},
+                   "storage": args.storage, "state_bytes": info["state_bytes"],
+                   "steps_per_launch": STEPS_PER_LAUNCH1},
         "hbm_gbps_algorithmic": round(achieved, 1),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
-                     "traffic": (round(traffic_b / (ms_step * 1e-3) / 1e9, 1)
+                     "traffic": (round(traffic_b / (ms_launch * 1e-3) / 1e9, 1)
                                  if traffic_b is not None else None)},
         "traffic_bytes_per_launch": traffic_b,
     }
@@ -512,10 +524,12 @@ def main():
     info = b.info(0)
     ms_step = ms / args.steps
     mlups = cells * args.steps / (ms * 1e-3) / 1e6
-    # per launch (one launch per step); a source adds its G reads (8 B a cell and term)
+    # per launch, which may take two steps; a source adds its G reads (8 B a cell and term)
     src_cells = sum(p.cells * source_terms(p) for p in problems)
     alg_bytes = algorithmic_bytes(problems, storage)
-    achieved = alg_bytes / (ms_step * 1e-3) / 1e9
+    per_launch = steps_per_launch(problems, storage)
+    ms_launch = ms_step * per_launch
+    achieved = alg_bytes / (ms_launch * 1e-3) / 1e9
     log(f"{args.storage}: {ms_step:.4f} ms/step, {mlups:.0f} MLUPS, {achieved:.0f} GB/s algorithmic "
         f"(launch rows/wave={info['rows_per_wave']} waves/block={info['waves_per_block']} "
         f"schedule={info['schedule']})")
@@ -546,7 +560,8 @@ def main():
                   "rel_l2_vs_fp64": l2, "rel_l2_after_steps": nsteps_l2}
 
     launch_s = f"{info['rows_per_wave']},{info['waves_per_block']},{info['schedule']},{info['xcd_remap']}"
-    traffic_b = measured_traffic(args.workload, args.storage, launch_s)
+    traffic_b = measured_traffic(args.workload, args.storage, launch_s,
+                                 kernel="k_step2" if per_launch == 2 else "k_step")
     out = {
         "metric": METRIC,
         "value": round(mlups, 1),
@@ -564,13 +579,13 @@ def main():
                    "lattice": f"D2Q{problems[0].q}", "storage": args.storage,
                    "state_bytes": state_bytes, "rows_per_wave": info["rows_per_wave"],
                    "waves_per_block": info["waves_per_block"], "schedule": info["schedule"],
-                   "launch_from": tuned_from,
+                   "launch_from": tuned_from, "steps_per_launch": per_launch,
                    # every instance x<->y symmetric: the binary32 and 16-bit steps share E between swapped pairs
                    "xy_symmetric": bool(info["xy_symmetric"])},
         "hbm_gbps_algorithmic": round(achieved, 1),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
-                     "traffic": (round(traffic_b / (ms_step * 1e-3) / 1e9, 1)
+                     "traffic": (round(traffic_b / (ms_launch * 1e-3) / 1e9, 1)
                                  if traffic_b is not None else None)},
         "traffic_bytes_per_launch": traffic_b,
         # timed steps replayed from the captured 32- and 4-step graphs vs launched one by one

@@ -144,20 +144,25 @@ int dugks3_reduce(dugks3_ctx* ctx, const double* ref_dev, double* mass, double* 
 /* Launch configuration: rows per block and planes swept per block (>= 1).
  * binary32: 2 to 4 rows; binary64: 1 or 2 rows.  D3Q15 and D3Q19 give each
  * row two or four waves, each holding a part of the directions: four for
- * D3Q19 in binary32 at 3 or 4 rows and in binary64 at 2 rows, and for D3Q15
- * the same on periodic meshes; two otherwise.  LDS per block: g of 3 planes
- * of the rows and the two halo rows, raw f~ of 1 or 2 staged planes (of the
- * rows and the halo rows with two waves a row; of the rows only with four,
- * whose halo rows go through registers), 4 face sums per row and wave, and
- * with the halo rows in registers their four quarter sums of phi (2 x 4 x 64
- * binary64).  Binary32 takes one staging slot where that alone brings a
- * block within 80 KiB (two blocks a CU), else two; binary64 one.  D3Q7
+ * D3Q19 in binary32 at 2 to 4 rows (with a source 3 or 4) and in binary64 at 2
+ * rows, and for D3Q15 the same on periodic meshes; two otherwise.  LDS per
+ * block: g of 3 planes of the rows and the two halo rows and 4 face sums per
+ * row and wave; with two waves a row raw f~ of 1 or 2 staged planes of the rows
+ * and the halo rows (binary32 takes one slot where that alone brings a block
+ * within 80 KiB, two blocks a CU, else two; binary64 one); with four, whose
+ * raw f~ goes through registers, the quarter sums of phi, (rows + 2) x 4 x 64
+ * binary64, and in binary32 with a source the cells' face coefficients of 3
+ * planes, 3 x (rows + 2) x 4 x 64 binary64.  Binary32 at 4 rows with mirror
+ * code and more than two terms (or more than four equilibrium coefficients and
+ * a source) stages 2 planes of the rows instead and keeps the halo rows'
+ * quarter sums only, 2 x 4 x 64 binary64.  D3Q7
  * gives each row one wave (binary32: 5 x (rows + 2) x q x 64 x 4
  * bytes of LDS; binary64: one more wave per halo row, 3 x (rows + 2) x q x
  * 64 x 8 bytes).  A launch needing more LDS than the device allows per block
- * is refused.  With a source the step takes the split-direction kernel's
- * instantiation with mirror code for every mesh and lattice (D3Q7 then with
- * two waves a row).  Defaults, with a source or without: 2 rows (binary64),
+ * is refused.  With a source D3Q15 and D3Q19 take the instantiation with
+ * mirror code where there are walls or more than four equilibrium
+ * coefficients, D3Q7 always (and the split-direction kernel, two waves a
+ * row).  Defaults, with a source or without: 2 rows (binary64),
  * 4 rows (binary32; D3Q15 with walls: 2); planes: D3Q15 and D3Q19 the power
  * of two in 4..128 that
  * minimises (rounds of blocks over 256 CUs) x (planes + 3), D3Q7 32 halved

@@ -10,7 +10,8 @@
 // whole-wave DPP shifts, as in the 2-D kernels.  D3Q15 and D3Q19 (both
 // storages) give each row two or four waves, each a part of the directions
 // (k_step3p): with two, raw f~ is staged through LDS with direct buffer-to-LDS
-// loads; with four, loaded into registers two planes ahead.  D3Q7, whose
+// loads; with four, loaded into registers two planes ahead (one instantiation
+// of the source step stages it: staged_rows).  D3Q7, whose
 // registers are no constraint, gives each row one wave: binary32 staged the
 // same way (k_step3s), binary64 with its window in registers and one wave on
 // each halo row (k_step3h).

@@ -7,8 +7,9 @@
 //     1..62 are updated and lanes 0 and 63 are halo columns; it marches down a
 //     chunk of rows.  f~ is read once per row per lane (coalesced 256-byte rows
 //     per plane) and the new f~ is written once: the state crosses HBM once in
-//     each direction per step, halo columns and the two halo rows per chunk
-//     aside.
+//     each direction per launch, halo columns and the halo rows of each chunk
+//     aside.  A launch takes one step (k_step) or two (k_step2: strips of 60
+//     columns, two halo lanes a side).
 //   - fbar+ of three rows (j-1, j, j+1) lives in registers.  Neighbouring
 //     columns are reached with whole-wave DPP shifts (wave_shr:1 / wave_shl:1),
 //     so no LDS and no barrier is used.
@@ -1049,8 +1050,9 @@ __device__ __forceinline__ void step_item(const InstDev* __restrict__ I, const W
 #endif
 // The 16-bit step is bound by its instruction count: three waves per SIMD
 // (168 registers, spills outside the row loop only) hide more of its latency
-// than two.  The source path holds more per row (G and its window): one wave
-// per SIMD, the full register file, no spills.
+// than two.  The source path holds more per row (G and its window): the full
+// register file, no spills, one wave per SIMD (two in binary32, whose 180 to 251
+// registers allow it).
 template <int ST, int NF> struct Occupancy {
   static constexpr int value = NF > 0 ? 1
                                : ST == DUGKS_F64 ? DUGKS_WAVES_PER_EU_F64
